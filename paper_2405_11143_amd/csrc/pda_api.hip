@@ -76,7 +76,7 @@ struct Plan {
   pda_plan_info info;
   int query_chunk;        // new tokens per work item: min(n, 16 / G)
   int num_query_chunks;   // ceil(n / query_chunk)
-  int chunks_per_group;   // 4; 8 with more than 4 chunks (two 16-row tiles per wavefront); 16 with more than 8
+  int chunks_per_group;   // 4; 8 with more than 4 chunks (two per wavefront); 16 with more than 8 (two workgroups)
   int num_chunk_groups;   // ceil(chunks / chunks_per_group): chunks per work item share its tiles
   int prefix_partitions;  // Pp: partitions of the longest shared prefix (0 without groups)
   int members_per_row_group;  // MR: members whose query rows (n G each) fill one prefix item of 64 rows
@@ -86,9 +86,10 @@ struct Plan {
   size_t slots;           // partial states: (Pp + P) per output row; 0 when nothing is split
 };
 
-// Workgroups the GPU runs at once in a step's pass-1 variant: 3 per compute
-// unit for items of up to 4 query chunks, 2 for the wide variant (243
-// VGPRs at D = 128), 1 for its 8-wavefront form.
+// Work items the GPU runs at once in a step's pass-1 variant: 3 per compute
+// unit for items of up to 4 query chunks, 2 for those of up to 8 (2 wide
+// workgroups per compute unit by their registers), 1 for those of up to 16
+// (two such workgroups each).
 int64_t concurrent_items(const Plan& plan) {
   if (plan.chunks_per_group > pda::kWideChunks) return kConcurrentItems / 3;
   if (plan.chunks_per_group > pda::kWaves) return kConcurrentItems * 2 / 3;
@@ -135,7 +136,7 @@ int make_plan(const pda_problem* p, const pda_prefix_groups* groups, Plan* plan)
   if (tp == 0) {
     const int64_t len = p->max_context_len > 0 ? p->max_context_len : 1;
     // (a product that would overflow only means: as long as allowed)
-    // items of more than 8 chunks (one 8-wavefront workgroup per compute
+    // items of more than 8 chunks (two workgroups each, one item per compute
     // unit) count 512 at once: long enough to amortise their start-up,
     // short enough that ragged contexts still balance
     const int64_t slots = cpg > pda::kWideChunks ? kConcurrentItems * 2 / 3 : kConcurrentItems;

@@ -11,8 +11,8 @@ constexpr int kBlockTokens = 16;  // tokens per KV-cache block
 constexpr int kWaveSize = 64;     // CDNA wavefront
 constexpr int kWaves = 4;         // wavefronts per partition workgroup
 constexpr int kMaxGroup = 16;     // query heads per KV head: one 16-row MFMA tile
-constexpr int kWideChunks = 2 * kWaves;  // query chunks of a work item when each wavefront folds two
-constexpr int kWide16Chunks = 4 * kWaves;  // the same with 8 wavefronts per workgroup (more than 8 chunks)
+constexpr int kWideChunks = 2 * kWaves;  // query chunks of a work item with more than 4: two per wavefront
+constexpr int kWide16Chunks = 4 * kWaves;  // with more than 8: two workgroups of kWideChunks
 constexpr int kOrderThreads = 1024;  // the work-order kernel is one workgroup of this size
 constexpr int kOrderBuckets = 256;   // size classes of its counting sort (partition blocks, capped)
 
@@ -42,8 +42,7 @@ struct StepArgs {
   int32_t num_query_tokens;  // n
   int32_t query_chunk;       // new tokens per query chunk (one 16-row tile): min(n, 16 / G)
   int32_t num_query_chunks;  // NQC = ceil(n / query_chunk)
-  int32_t chunks_per_group;  // CPG: 4; 8 when NQC > 4 (each wavefront then folds two tiles); 16 when NQC > 8
-                             // (8 wavefronts of two tiles)
+  int32_t chunks_per_group;  // CPG: 4; 8 when NQC > 4 (two chunks per wavefront); 16 when NQC > 8 (two workgroups)
   int32_t num_chunk_groups;  // NCG = ceil(NQC / CPG): chunks of one work item share its K/V tiles
   int32_t partition_tokens;  // T_p, multiple of 16
   int32_t num_partitions;    // P = max(1, ceil(max_context_len / T_p))
@@ -138,6 +137,7 @@ hipError_t launch_append(const StepArgs& a, const uint16_t* k_new, const uint16_
                          uint16_t* v_cache, int head_dim, hipStream_t stream);
 hipError_t launch_order(const StepArgs& a, hipStream_t stream);
 hipError_t launch_partition(const StepArgs& a, int head_dim, hipStream_t stream);
+hipError_t launch_wide(const StepArgs& a, int head_dim, hipStream_t stream);  // items of more than 4 chunks, no groups
 hipError_t launch_merge(const StepArgs& a, int head_dim, hipStream_t stream);
 
 }  // namespace pda

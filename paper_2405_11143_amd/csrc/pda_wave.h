@@ -215,11 +215,9 @@ struct WaveAttention {
   // The scaled scores are formed here, in the MFMAs' own basic block: the
   // compiler did not insert the wait states a VALU read of an MFMA result
   // needs when the first such read came after the tail branch of probs.
-  // PRIO: the MFMAs issue at raised wave priority (as in pv_staged).
-  template <int NB, bool PRIO = false>
+  template <int NB>
   __device__ __forceinline__ void scores(const uint4 (&kr)[NB][NC], float (&sc)[NB][4]) const {
     floatx4_t acc[NB];
-    if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       acc[b] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -227,7 +225,6 @@ struct WaveAttention {
       for (int c = 0; c < NC; ++c)
         acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kr[b][c]), qa[c], acc[b], 0, 0, 0);
     }
-    if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -332,12 +329,7 @@ struct WaveAttention {
 
   // O^T += V^T P^T for a staged pair (fragments from v_frags), with D/16
   // MFMA f32_16x16x32_bf16 per half of P.  In a tail pair, fragment elements
-  // of tokens at or past l_vis are zeroed first.  PRIO: the wavefront issues
-  // these MFMAs at raised priority (for workgroups of 8 wavefronts, whose
-  // pairs on a SIMD fold the same steps; with the score MFMAs raised too,
-  // chunked prefill and long CoT with 64 new tokens ran 5% faster on MI355X,
-  // while workgroups of 4 gained nothing and lost 4.6% with 16 new tokens).
-  template <bool PRIO = false>
+  // of tokens at or past l_vis are zeroed first.
   __device__ __forceinline__ void pv_staged(uint4 (&aw)[VT], const PFrag<2>& f, bool tail, int tok0, int l_vis) {
     if (tail) {
       asm volatile("");  // a branch, as in softmax
@@ -355,14 +347,12 @@ struct WaveAttention {
     }
     const bf16x8_t bh = __builtin_bit_cast(bf16x8_t, make_uint4(f.hw[0], f.hw[1], f.hw[2], f.hw[3]));
     const bf16x8_t bl = __builtin_bit_cast(bf16x8_t, make_uint4(f.lw[0], f.lw[1], f.lw[2], f.lw[3]));
-    if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int t = 0; t < VT; ++t) {
       const bf16x8_t a = __builtin_bit_cast(bf16x8_t, aw[t]);
       o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bh, o[t], 0, 0, 0);
       o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, o[t], 0, 0, 0);
     }
-    if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
   }
 
   // Fold one block (logical tokens tok0 .. tok0+15) into the state.  `L` is

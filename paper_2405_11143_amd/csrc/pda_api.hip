@@ -219,6 +219,7 @@ void fill_args(const pda_problem* p, const Plan* plan, void* ws, pda::StepArgs* 
   args->num_q_heads = p->num_q_heads;
   args->num_kv_heads = p->num_kv_heads;
   args->group = p->num_q_heads / p->num_kv_heads;
+  args->group_inverse = (65536 + args->group - 1) / args->group;
   args->num_blocks = p->num_blocks;
   args->max_blocks_per_seq = p->max_blocks_per_seq;
   args->max_context_len = p->max_context_len;

@@ -36,6 +36,7 @@ struct StepArgs {
   int32_t num_q_heads;     // Hq
   int32_t num_kv_heads;    // Hkv
   int32_t group;           // G = Hq / Hkv
+  int32_t group_inverse;   // ceil(2^16 / G): x / G = x * group_inverse >> 16 for x < 2^12
   int32_t num_blocks;
   int32_t max_blocks_per_seq;
   int32_t max_context_len;

@@ -81,10 +81,10 @@ struct Staging {
 
 // Which paths a launch compiles.  A launch whose items all have one tile
 // (every decode step without shared-prefix groups) compiles the register
-// path only (138 VGPRs at D = 128, 33 KiB of LDS); with up to 4 query chunks
+// path only (139 VGPRs at D = 128, 33 KiB of LDS); with up to 4 query chunks
 // per item both paths are compiled (167 VGPRs, 50.5 KiB); with more, which
 // comes here only with shared-prefix groups, the wide variant also folds two
-// tiles per wavefront (243 VGPRs, 2 workgroups per compute unit).
+// tiles per wavefront (241 VGPRs, 2 workgroups per compute unit).
 // Staging takes 2 blocks per step, so three
 // staging buffers (49.5 KiB at D = 128) still leave room for 3 workgroups
 // per compute unit; 4 blocks per step at 2 workgroups per compute unit
@@ -408,17 +408,14 @@ __device__ __forceinline__ void store_new_token(const StepArgs& a, int b, int g,
 }
 
 template <int D, int MODE>
-__device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int item) {
+__device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, int b, int p) {
   PassShared<D>& sh = lds.sh;
   using WA = WaveAttention<D>;
   const int Hq = a.num_q_heads;
   const int G = a.group;
-  const int HC = a.num_kv_heads * a.num_chunk_groups;
-  const int gc = item % HC;  // item = (p * B + b) * HC + g * NCG + chunk group
-  const int b = (item / HC) % a.num_seqs;
-  const int p = item / (HC * a.num_seqs);
-  const int g = gc / a.num_chunk_groups;
-  const int cg = gc % a.num_chunk_groups;
+  // gc = g * NCG + chunk group (up to 4 chunks, and 8 with groups: one chunk group)
+  const int g = MODE == kModeRegister ? gc : gc / a.num_chunk_groups;
+  const int cg = MODE == kModeRegister ? 0 : gc % a.num_chunk_groups;
   const int nq = a.num_query_tokens;
   const int CPG = a.chunks_per_group;
   // query chunks (16-row tiles) of the item: always one in the register-only variant
@@ -476,8 +473,8 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int item)
     return p < parts ? (min(lv, t0 + (p + 1) * Tp) + kBlockTokens - 1) / kBlockTokens : 0;
   };
 
-  // One chunk's rows in a wavefront: lane row n repeats real rows past the
-  // chunk's last one.
+  // One chunk's rows in a wavefront: lane rows past the chunk's last one
+  // repeat it.
   struct ChunkRows {
     int c, rows, l_vis, l_first, nparts;
   };
@@ -486,9 +483,10 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int item)
     const int nv = min(a.query_chunk, nq - i0);
     ChunkRows cr{c, nv * G, chunk_visible(a, L, c), 0, parts_of(c)};
     cr.l_first = cr.l_vis - nv + 1;
-    const int r = (lane & 15) % cr.rows;
-    const int qi = i0 + r / G;
-    wv.start(a.q + (((size_t)b * nq + qi) * Hq + (size_t)g * G + r % G) * D, nq - 1 - qi);
+    const int r = min(lane & 15, cr.rows - 1);
+    const int ri = r * a.group_inverse >> 16;  // r / G
+    const int qi = i0 + ri;
+    wv.start(a.q + (((size_t)b * nq + qi) * Hq + (size_t)g * G + (r - ri * G)) * D, nq - 1 - qi);
     return cr;
   };
 
@@ -499,6 +497,51 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int item)
   auto epilogue = [&](const WA& wv, int rows, bool publishes, int t_first, int nt, int sl, int& any_bad, bool first) {
     if (publishes) publish(sh, wv, w, lane, rows);
     __syncthreads();
+    if constexpr (MODE == kModeRegister) {
+      // One tile of at most 16 rows: every thread forms its rows' weights by
+      // itself (as row_weights and combine do, in the same order), one LDS
+      // round trip and no second barrier.  A small step is a chain of
+      // latencies: with this and without the integer divisions on the way to
+      // its first load, 4 sequences of up to 257 tokens took 4.3 us a step
+      // instead of 5.2, and 16 layers of 6 sequences 157 us instead of 179.
+      int bad = 0;
+#pragma unroll
+      for (int x = 0; x < kWaves; ++x) bad |= sh.bad[x];
+      const bool single = nparts_max == 1 && min(t0_all, chunk_visible(a, L, 0)) == 0;
+      for (int idx = tid; idx < rows * (D / 4); idx += kWaves * kWaveSize) {  // 4 columns per thread
+        const int h = idx / (D / 4);
+        const int d0 = 4 * (idx % (D / 4));
+        float m[kWaves], l[kWaves];
+        f32x4_t ow[kWaves];
+#pragma unroll
+        for (int x = 0; x < kWaves; ++x) {
+          m[x] = sh.m[x][h];
+          l[x] = sh.l[x][h];
+          ow[x] = *reinterpret_cast<const f32x4_t*>(&sh.o[x][h][d0]);
+        }
+        float M = WA::kFloor, lsum = 0.f, acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < kWaves; ++x) M = fmaxf(M, m[x]);
+#pragma unroll
+        for (int x = 0; x < kWaves; ++x) {
+          const float sc = exp2_fast(m[x] - M);
+          lsum = fmaf(sc, l[x], lsum);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = fmaf(sc, ow[x][e], acc[e]);
+        }
+        if (bad) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = __builtin_nanf("");
+        }
+        const int hi = h * a.group_inverse >> 16;  // h / G
+        const size_t row = ((size_t)b * nq + hi) * Hq + (size_t)g * G + (h - hi * G);
+        if (single)
+          store_final4(a.out + row * D + d0, acc, lsum);
+        else
+          store_partial4(a, row * a.slots_per_row + a.prefix_partitions + p, d0, D, acc, M, lsum);
+      }
+      return;
+    }
     row_weights(sh, nt, sl);
     if (first) {
       any_bad = 0;
@@ -667,18 +710,25 @@ __global__ void __launch_bounds__(kWaves * kWaveSize)
 __attribute__((amdgpu_waves_per_eu(MODE == kModeWide ? 2 : 3)))
 partition_kernel(const StepArgs a) {
   __shared__ __align__(16) PassLds<D, MODE> lds;
-  const int item = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;  // no order: every item runs at once
+  if (!a.order) {  // every item runs at once: a workgroup's place in the grid is its item (no divisions)
+    regular_item<D, MODE>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
+    return;
+  }
+  const int item = a.order[blockIdx.x];
   // an order reused from an earlier call is the caller's contract; never step outside the items
   if ((unsigned)item >= (unsigned)(a.num_regular_items + a.num_prefix_items)) return;
-  if (item < a.num_regular_items)
-    regular_item<D, MODE>(a, lds, item);
-  else
+  if (item < a.num_regular_items) {  // item = (p * B + b) * HC + gc
+    const int HC = a.num_kv_heads * a.num_chunk_groups;
+    regular_item<D, MODE>(a, lds, item % HC, (item / HC) % a.num_seqs, item / (HC * a.num_seqs));
+  } else {
     prefix_item<D, MODE>(a, lds, item - a.num_regular_items);
+  }
 }
 
 template <int D>
 hipError_t launch_d(const StepArgs& a, hipStream_t stream) {
-  const unsigned grid = (unsigned)a.num_regular_items + (unsigned)a.num_prefix_items;
+  const dim3 grid = a.order ? dim3((unsigned)a.num_regular_items + (unsigned)a.num_prefix_items)
+                            : dim3(a.num_kv_heads * a.num_chunk_groups, a.num_seqs, a.num_partitions);
   // which kinds of items the step has: a regular item has one tile when its
   // chunk group holds one query chunk; a prefix item may have one tile
   // whenever groups exist (a row group can be small) and several when the
@@ -690,11 +740,11 @@ hipError_t launch_d(const StepArgs& a, hipStream_t stream) {
       (groups && (int64_t)min(a.max_group_size, a.members_per_row_group) * a.num_query_tokens * a.group > kRows);
   const dim3 block(kWaves * kWaveSize);
   if (a.chunks_per_group > kWaves)
-    hipLaunchKernelGGL((partition_kernel<D, kModeWide>), dim3(grid), block, 0, stream, a);
+    hipLaunchKernelGGL((partition_kernel<D, kModeWide>), grid, block, 0, stream, a);
   else if (one && !several)
-    hipLaunchKernelGGL((partition_kernel<D, kModeRegister>), dim3(grid), block, 0, stream, a);
+    hipLaunchKernelGGL((partition_kernel<D, kModeRegister>), grid, block, 0, stream, a);
   else
-    hipLaunchKernelGGL((partition_kernel<D, kModeMixed>), dim3(grid), block, 0, stream, a);
+    hipLaunchKernelGGL((partition_kernel<D, kModeMixed>), grid, block, 0, stream, a);
   return hipGetLastError();
 }
 

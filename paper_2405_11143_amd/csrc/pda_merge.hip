@@ -6,10 +6,18 @@
 // m_k = -1e30, l_k = 0, O_k = 0).  Softmax over the whole context is recovered
 // exactly by rescaling every partition to the common maximum M = max_k m_k:
 //   out = sum_k 2^(m_k - M) O_k / sum_k 2^(m_k - M) l_k.
-// The output sum runs in ascending k and the denominator in a fixed
-// butterfly, so the result is reproducible.  One wavefront per output row
-// (sequence, new token, query head), 4 rows per workgroup; each lane owns
-// D/64 output columns.
+// Both sums run in a fixed order, so the result is reproducible.  One
+// wavefront per output row (sequence, new token, query head), 4 rows per
+// workgroup.
+//
+// A small step's merge is a chain of memory latencies, so the chain is kept
+// short.  A row's states sit in its own slots_per_row slots (its group's prefix
+// partitions, then its own), whatever it sees: the maxima and denominators of
+// all slots (one per lane) and the outputs of the first kSpec are loaded
+// before the row's length is known, and slots that turn out to hold nothing
+// get weight 0 and are left out by selection.  Outputs are read 16 bytes per
+// lane, several slots per instruction, and past the first kSpec slots
+// kInFlight instructions at a time.
 #include "pda_internal.h"
 
 namespace pda {
@@ -27,69 +35,24 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
-// Merge n partitions of one row: partition k (k < n) sits at state index
-// first + k for k < n_pre (the group's prefix partitions) and at
-// first + gap + k after them (the row's own partitions); the outputs sit at
-// D times those indices in part_o.
-template <int D>
-__device__ __forceinline__ void merge_partitions(const StepArgs& a, size_t first, int n_pre, int gap, int n,
-                                                 float* orow) {
-  constexpr int PER = D / kWaveSize;
-  const int lane = threadIdx.x & (kWaveSize - 1);
-  auto slot = [&](int k) { return first + (size_t)k + (k >= n_pre ? gap : 0); };
-  // States are read lane-parallel (lane x holds partition p0 + x), so the
-  // dependent chain is states -> outputs, whatever n is.
-  float M = -__builtin_huge_valf();
-  for (int p0 = 0; p0 < n; p0 += kWaveSize)
-    if (p0 + lane < n) M = fmaxf(M, a.part_m[slot(p0 + lane)]);
-  M = wave_max(M);
-  float acc[PER];
-#pragma unroll
-  for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-  float lpart = 0.f;
-  for (int p0 = 0; p0 < n; p0 += kWaveSize) {
-    const int p = p0 + lane;
-    const float wgt = p < n ? __builtin_amdgcn_exp2f(a.part_m[slot(p)] - M) : 0.f;  // 2^(m_p - M)
-    if (p < n) lpart = fmaf(wgt, a.part_l[slot(p)], lpart);
-    const int cnt = min(kWaveSize, n - p0);
-    for (int x = 0; x < cnt; ++x) {
-      const float sc = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt), x));
-      const float* src = a.part_o + slot(p0 + x) * D + lane * PER;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) acc[e] = fmaf(sc, src[e], acc[e]);
-    }
-  }
-  const float lsum = wave_sum(lpart);
-  const bool pos = lsum > 0.f;  // 0: the row sees nothing
-  if constexpr (PER == 2)
-    store_nt2(orow + lane * PER, pos ? acc[0] / lsum : acc[0], pos ? acc[1] / lsum : acc[1]);
-  else
-    __builtin_nontemporal_store(pos ? acc[0] / lsum : acc[0], orow + lane);
-}
-
 __device__ __forceinline__ int clamped_len(const StepArgs& a, int b) {
   const int L = a.lens[b];
   return L < 0 ? 0 : (L > a.max_context_len ? a.max_context_len : L);
 }
 
+constexpr int kMergeRows = 4;  // rows (wavefronts) per workgroup
+constexpr int kSpec = 8;       // slots whose outputs are loaded before the length is known
+constexpr int kInFlight = 4;   // output loads in flight past them
+
 // Output row (b, i, h), row = (b * n + i) * Hq + h, has its partial states
 // at slots row * S .. row * S + S - 1 (S = slots_per_row): first the prefix
 // partitions of its group, then, from slot row * S + Pp, its own partitions
 // (as many as the query chunk of new token i sees after the prefix).
-//
-// Without groups and with at most kSpec slots per row (every split decode
-// step up to 8 partitions), the row's states are loaded before its length
-// is known -- they lie in the row's own slots, whatever it sees -- so that
-// the length, the states and the outputs take one memory round trip instead
-// of a chain of them; the arithmetic is that of merge_partitions, in the
-// same order.
-constexpr int kSpec = 8;
-
-constexpr int kMergeRows = 4;  // rows (wavefronts) per workgroup
-
 template <int D>
-__global__ void __launch_bounds__(kMergeRows * kWaveSize) merge_kernel(const StepArgs a) {
-  constexpr int PER = D / kWaveSize;
+__global__ void __launch_bounds__(kMergeRows * kWaveSize) __attribute__((amdgpu_waves_per_eu(5))) merge_kernel(const StepArgs a) {
+  constexpr int LPS = D / 4;             // lanes per slot: 4 columns each
+  constexpr int SPI = kWaveSize / LPS;   // slots per load instruction
+  constexpr int NS = kSpec / SPI;
   const int row = blockIdx.x * kMergeRows + (threadIdx.x >> 6);
   const int lane = threadIdx.x & (kWaveSize - 1);
   if ((size_t)row >= (size_t)a.num_seqs * a.num_query_tokens * a.num_q_heads) return;  // spare wavefronts
@@ -97,19 +60,21 @@ __global__ void __launch_bounds__(kMergeRows * kWaveSize) merge_kernel(const Ste
   const int b = row / (a.num_q_heads * a.num_query_tokens);
   const int S = a.slots_per_row;
   const size_t first = (size_t)row * S;
-  const bool spec = a.num_groups == 0 && S <= kSpec;  // uniform
-  float m_s = -__builtin_huge_valf(), l_s = 0.f;
-  float o_s[kSpec][PER];
-  if (spec) {
-    if (lane < S) {
-      m_s = a.part_m[first + lane];
-      l_s = a.part_l[first + lane];
-    }
-#pragma unroll
-    for (int x = 0; x < kSpec; ++x)
-#pragma unroll
-      for (int e = 0; e < PER; ++e) o_s[x][e] = x < S ? a.part_o[(first + x) * D + lane * PER + e] : 0.f;
+  const int sub = lane / LPS;         // the lane's slot of a load instruction
+  const int d0 = 4 * (lane % LPS);    // its columns
+  const float* src = a.part_o + (first + sub) * D + d0;  // slot s + sub at src + s * D
+  constexpr float kNone = -__builtin_huge_valf();
+
+  float m_first = kNone, l_first = 0.f;
+  if (lane < S) {
+    m_first = a.part_m[first + lane];
+    l_first = a.part_l[first + lane];
   }
+  f32x4_t o_s[NS];
+#pragma unroll
+  for (int x = 0; x < NS; ++x)
+    if (x * SPI + sub < S) o_s[x] = *reinterpret_cast<const f32x4_t*>(src + (size_t)(x * SPI) * D);
+
   const int L = clamped_len(a, b);
   const int vis = chunk_visible(a, L, i / a.query_chunk);
   if (vis <= 0) return;  // pass 1 wrote zeros
@@ -118,32 +83,73 @@ __global__ void __launch_bounds__(kMergeRows * kWaveSize) merge_kernel(const Ste
   const int n_pre = (t0 + Tp - 1) / Tp;
   const int n_own = (vis - t0 + Tp - 1) / Tp;
   if (n_pre == 0 && n_own <= 1) return;  // pass 1 wrote the final row
-  float* orow = a.out + (size_t)row * D;
-  if (!spec) {
-    merge_partitions<D>(a, first, n_pre, a.prefix_partitions - n_pre, n_pre + n_own, orow);
-    return;
+  const int own = a.prefix_partitions, own_end = own + n_own;
+  auto valid = [&](int s) { return s < n_pre || (s >= own && s < own_end); };
+  // the maximum and the denominator of slots s0 .. s0 + 63, one per lane
+  auto state = [&](int s0, float& m, float& l) {
+    const int s = s0 + lane;
+    if (s0 == 0) {
+      m = m_first, l = l_first;
+    } else if (s < S) {
+      m = a.part_m[first + s], l = a.part_l[first + s];
+    }
+    if (!valid(s)) m = kNone, l = 0.f;
+  };
+  float M = kNone;
+  for (int s0 = 0; s0 < own_end; s0 += kWaveSize) {
+    float m = kNone, l = 0.f;
+    state(s0, m, l);
+    M = fmaxf(M, m);
   }
-  const int n = n_own;  // no groups: the row's partitions are slots 0 .. n - 1 (n <= S)
-  const float M = wave_max(lane < n ? fmaxf(-__builtin_huge_valf(), m_s) : -__builtin_huge_valf());
-  const float wgt = lane < n ? __builtin_amdgcn_exp2f(m_s - M) : 0.f;  // 2^(m_p - M)
-  const float lpart = lane < n ? fmaf(wgt, l_s, 0.f) : 0.f;
-  float acc[PER];
+  M = wave_max(M);
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  float lpart = 0.f;
+  auto add = [&](bool in, float wgt, const f32x4_t& v) {
+    if (in) {
 #pragma unroll
-  for (int e = 0; e < PER; ++e) acc[e] = 0.f;
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(wgt, v[e], acc[e]);
+    }
+  };
+  for (int s0 = 0; s0 < own_end; s0 += kWaveSize) {
+    float m = kNone, l = 0.f;
+    state(s0, m, l);
+    const float wgt = __builtin_amdgcn_exp2f(m - M);  // 2^(m - M), 0 for a slot that holds nothing
+    lpart = fmaf(wgt, l, lpart);
+    const int end = min(kWaveSize, own_end - s0);
+    int x0 = 0;
+    if (s0 == 0) {
 #pragma unroll
-  for (int x = 0; x < kSpec; ++x) {
-    if (x < n) {
-      const float sc = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt), x));
+      for (int x = 0; x < NS; ++x) {
+        auto of_lane = [&](int i) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wgt), i)); };
+        float w_x = of_lane(x * SPI);  // the weight of slot x SPI + sub
 #pragma unroll
-      for (int e = 0; e < PER; ++e) acc[e] = fmaf(sc, o_s[x][e], acc[e]);
+        for (int i = 1; i < SPI; ++i) w_x = sub == i ? of_lane(x * SPI + i) : w_x;
+        add(valid(x * SPI + sub), w_x, o_s[x]);
+      }
+      x0 = kSpec;
+    }
+    for (; x0 < end; x0 += kInFlight * SPI) {
+      f32x4_t v[kInFlight];
+      auto slot = [&](int x) { return x0 + x * SPI + sub; };  // of these 64
+      auto in = [&](int x) { return slot(x) < kWaveSize && valid(s0 + slot(x)); };
+#pragma unroll
+      for (int x = 0; x < kInFlight; ++x)
+        if (in(x)) v[x] = *reinterpret_cast<const f32x4_t*>(src + (size_t)(s0 + x0 + x * SPI) * D);
+#pragma unroll
+      for (int x = 0; x < kInFlight; ++x) add(in(x), __shfl(wgt, slot(x) & (kWaveSize - 1)), v[x]);
     }
   }
+#pragma unroll
+  for (int o = LPS; o < kWaveSize; o <<= 1)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
   const float lsum = wave_sum(lpart);
   const bool pos = lsum > 0.f;  // 0: the row sees nothing
-  if constexpr (PER == 2)
-    store_nt2(orow + lane * PER, pos ? acc[0] / lsum : acc[0], pos ? acc[1] / lsum : acc[1]);
-  else
-    __builtin_nontemporal_store(pos ? acc[0] / lsum : acc[0], orow + lane);
+  if (sub == 0) {
+    float* orow = a.out + (size_t)row * D + d0;
+    store_nt4(orow, pos ? acc[0] / lsum : acc[0], pos ? acc[1] / lsum : acc[1], pos ? acc[2] / lsum : acc[2],
+              pos ? acc[3] / lsum : acc[3]);
+  }
 }
 
 }  // namespace

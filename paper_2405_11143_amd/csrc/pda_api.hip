@@ -41,6 +41,25 @@ namespace {
 // The result is rounded up to kPartitionQuantum tokens, at least
 // kMinPartitionTokens and never longer than the longest context (then there
 // is one partition and no merge pass).
+//
+// A step with few (sequence, KV head) pairs instead takes the partitions that
+// make its items about one per slot of the GPU (slots_at_once), when that
+// fills at least kFillNum / kFillDen of the slots: a compute unit reads at
+// most about 64 KB at a time whatever its workgroups ask for (67 GB/s from
+// HBM), so a second item on some of them doubles the step's time, and the
+// work-order launch that few items do without is a large part of it.  GPU
+// time on MI355X, 32 / 8 heads, contexts uniform (log-uniform) up to the
+// maximum, this rule against the share: 4 sequences of up to 4096 tokens
+// 12.3 / 14.5 us (11.7 / 13.1), 8 of 4096 18.5 / 22.9 (16.8 / 17.7), 4 of 4096
+// with 64 new tokens 42.4 / 53.9 (38.6 / 37.6), 16 of 1024 with 64 new tokens
+// 38.8 / 69.2 (36.3 / 46.8).  Not where the slots stay less full (96 pairs in
+// 192 of 256 slots, contexts of 8192: 50.8 / 46.1 us), nor in partitions above
+// kFillMaxTokens: few long items wait for the longest one when the contexts
+// are log-uniform (8 of 16384 in partitions of 4096: 54.4 / 58.2, but 47.4 /
+// 34.0 us).  Contexts that are not worth a merge pass (about 3 us) stay whole:
+// up to kWholeTokens (4 sequences of 512: 7.5 / 9.0 us), and where there is no
+// second item per slot to be had up to kOneItemTokens (32 of 1024: 16.8 / 22.4
+// us; 64: 31.0 / 35.3; 64 of 2048: 56.8 / 58.2, but log-uniform 39.8 / 35.2).
 // Longest context a descriptor may announce: keeps every token sum of the
 // kernels (a position plus a partition size) far inside int32.
 constexpr int32_t kMaxContextTokens = 1 << 28;
@@ -50,6 +69,12 @@ constexpr int64_t kRowsShareNum = 13, kRowsShareDen = 10;
 constexpr int kMinPartitionTokens = 256;
 constexpr int kPartitionQuantum = 256;
 constexpr int64_t kConcurrentItems = 768;  // 256 compute units x 3 workgroups of 4 wavefronts
+constexpr int64_t kFillNum = 17, kFillDen = 20;
+constexpr int kWholeTokens = 640;          // one-tile contexts left whole
+constexpr int kOneItemTokens = 1024;       // ... and when there is one for each slot
+constexpr int kFillMaxTokens = 1024;
+constexpr int kWideManyMinTokens = 1024;   // shortest partition of many wide items (their states cost more)
+constexpr int64_t kWideManyUnits = 64;
 constexpr int64_t kPrefixItemRows = 64;    // query rows of one prefix item: 4 tiles of 16
 
 int query_tokens(const pda_problem* p) { return p->num_query_tokens > 0 ? p->num_query_tokens : 1; }
@@ -116,6 +141,22 @@ int64_t mul_sat(int64_t a, int64_t b) {
   return a > kSat / b ? kSat : std::min(kSat, a * b);
 }
 
+// Partition size that gives each slot of the GPU one item (0: the step has
+// too many pairs, or cannot fill the slots evenly).
+int64_t filling_partition(const pda_prefix_groups* groups, int nqc, int cpg, int64_t units, int64_t len) {
+  if (groups || units == 0 || (nqc > 1 && cpg == pda::kWaves)) return 0;  // (staged items run 3 to a compute unit)
+  // compute units for one-tile items; pairs of wide workgroups (or one of them) otherwise
+  const int64_t slots_at_once = cpg == pda::kWideChunks ? kConcurrentItems * 2 / 3 : kConcurrentItems / 3;
+  const bool one_each = 2 * units > slots_at_once && units <= kConcurrentItems;
+  if (nqc == 1 && (len <= kWholeTokens || (one_each && len <= kOneItemTokens))) return len;
+  const int64_t pieces = slots_at_once / units;
+  if (pieces == 0 || units * pieces * kFillDen < slots_at_once * kFillNum || (nqc == 1 && pieces == 1)) return 0;
+  // (to the nearest quantum: contexts are ragged, so a few items more than slots are mostly empty ones)
+  int64_t tokens = std::max<int64_t>(1, (len / pieces + kPartitionQuantum / 2) / kPartitionQuantum) * kPartitionQuantum;
+  if (nqc > 1 && units >= kWideManyUnits) tokens = std::max<int64_t>(tokens, kWideManyMinTokens);
+  return tokens <= kFillMaxTokens ? tokens : 0;
+}
+
 int make_plan(const pda_problem* p, const pda_prefix_groups* groups, Plan* plan) {
   int rc = check_problem(p);
   if (rc != PDA_OK) return rc;
@@ -143,6 +184,8 @@ int make_plan(const pda_problem* p, const pda_prefix_groups* groups, Plan* plan)
     int64_t share = units > (INT64_MAX / 4) / len ? INT64_MAX / 4 : (units * len / 2 + slots - 1) / slots;
     const int64_t item_rows = (int64_t)std::min(nqc, cpg) * qc * G;
     if (item_rows >= pda::kMaxGroup) share = share * kRowsShareNum / kRowsShareDen;
+    const int64_t fill = filling_partition(groups, nqc, cpg, units, len);
+    if (fill > 0) share = fill;
     const int64_t cap = item_rows >= kWideItemRows ? kMaxContextTokens : kMaxPartitionTokens;
     if (share > cap) {
       const int64_t pieces = (len + cap - 1) / cap;

@@ -1,0 +1,32 @@
+"""The partition sizes of steps with few (sequence, KV head) pairs, and that
+the rule for them stops where the general one takes over (no GPU)."""
+import pytest
+
+import paper_2405_11143_amd as pda
+
+
+def plan(B, Hq, Hkv, max_len, n=1, D=128):
+    info = pda.pda_plan(pda.make_problem(B, Hq, Hkv, D, 1 << 20, -(-max_len // 16), max_len, num_query_tokens=n))
+    return info["partition_tokens"], info["num_partitions"]
+
+
+@pytest.mark.parametrize("args,want", [
+    ((4, 32, 8, 640), (640, 1)),         # short contexts stay whole
+    ((4, 32, 8, 641), (256, 3)),         # 256 slots / 32 pairs = 8 pieces, at least 256 tokens
+    ((4, 32, 8, 4096), (512, 8)),
+    ((4, 32, 8, 8192), (1024, 8)),
+    ((4, 32, 8, 8400), (1024, 9)),       # to the nearest 256
+    ((4, 32, 8, 16384), (512, 32)),      # 2048 would be too long: the share
+    ((8, 32, 8, 4096), (1024, 4)),
+    ((12, 32, 8, 4096), (256, 16)),      # 96 pairs x 2 leave a quarter of the slots empty: the share
+    ((17, 32, 8, 1024), (1024, 1)),      # no second item per slot
+    ((17, 32, 8, 1025), (256, 5)),
+    ((96, 32, 8, 1024), (1024, 1)),
+    ((97, 32, 8, 1024), (768, 2)),       # more pairs than items run at once: the share
+    ((4, 32, 8, 4096, 64), (512, 8)),    # items of two workgroups, one per compute unit
+    ((4, 32, 8, 4096, 32), (256, 16)),   # of one: 512 slots
+    ((16, 32, 8, 1024, 64), (1024, 1)),  # many wide rows are not split further
+    ((4, 32, 8, 1024, 5), (256, 4)),     # staged items of 2-4 chunks: the share
+])
+def test_partition_choice(args, want):
+    assert plan(*args) == want

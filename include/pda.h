@@ -268,7 +268,8 @@ int pda_append_kv(const pda_problem *prob, const void *k_new, const void *v_new,
  * (num_query_tokens 0 or 1; the KV-cache management and attention of one
  * rollout step, Section 3.2 and Appendix C).  When every pass-1 work item of
  * the step runs at once (a small batch, where each launch is a large part of
- * the step), the append is folded into pass 1: the wavefront that reads
+ * the step), or contexts are split into several partitions (so that few items
+ * wait for the store), the append is folded into pass 1: the wavefront that reads
  * position L - 1 of a (sequence, KV head) first stores the new token's K and
  * V rows there, and the step needs no append launch.  Larger steps run the
  * append kernel first.  Arguments are those of pda_append_kv and pda_decode;

@@ -348,15 +348,19 @@ hipError_t launch_append_of(const pda_problem* p, const pda::StepArgs& args, con
 }
 
 // Whether a step folds its KV append into pass 1: one new token per
-// sequence, and every work item runs at once (a small batch, where the
+// sequence, and either every work item runs at once (a small batch, where the
 // append's own launch is a large part of the step: the 32-layer step of a
-// 4-sequence batch ran 1.6x faster as one graph with the appends folded).
-// In larger steps each item's wavefront that stores the new rows waits for
-// its stores before it streams, and on MI355X that cost the Llama-3-8B step
-// 3%, more than the separate append kernel (3.4 us), so there the append
-// keeps its own launch.
+// 4-sequence batch ran 1.6x faster as one graph with the appends folded), or
+// contexts are split so that at most one item in kFoldPartitions stores.  The
+// item's wavefront that stores the new rows waits for its stores before it
+// streams: where every item does (the Llama-3-8B step, one partition) that
+// cost 3% on MI355X, more than the separate append kernel (3.4 us); where one
+// in 22 does (8 contexts of up to 16384 tokens) the launch saved is 37.9 ->
+// 34.9 us, with 3-6 partitions 80.7 -> 79.0 (48 contexts of 4096) and 193 ->
+// 191.5 us (64 of 8192).
+constexpr int kFoldPartitions = 3;
 bool folds_append(const pda_problem* p, const Plan& plan) {
-  return query_tokens(p) == 1 && plan.items <= (size_t)concurrent_items(plan);
+  return query_tokens(p) == 1 && (plan.items <= (size_t)concurrent_items(plan) || plan.info.num_partitions >= kFoldPartitions);
 }
 
 // Let pass 1 store the step's new K/V rows (one new token per sequence, no

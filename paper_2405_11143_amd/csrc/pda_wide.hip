@@ -343,7 +343,9 @@ wide_kernel(const StepArgs a) {
 
   for (int jw = J0; jw < J1; jw += kWindow) {
     const int jwe = min(J1, jw + kWindow);
-    for (int x = tid; x < kWindow; x += kWaves * kWaveSize) {
+    // (as many as the steps and the loads issued past them read, by 64)
+    const int n_ids = min(kWindow, (jwe - jw + kBuffers * kStageBlocks + kWaveSize) / kWaveSize * kWaveSize);
+    for (int x = tid; x < n_ids; x += kWaves * kWaveSize) {
       const int id = table_row[min(jw + x, jwe - 1)];  // past the end: the last block again (masked)
       const bool ok = (unsigned)id < (unsigned)a.num_blocks;  // never read outside the pool
       bad |= !ok;

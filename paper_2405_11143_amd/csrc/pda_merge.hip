@@ -18,21 +18,37 @@
 // get weight 0 and are left out by selection.  Outputs are read 16 bytes per
 // lane, several slots per instruction, and past the first kSpec slots
 // kInFlight instructions at a time.
+//
+// With many rows (several new tokens per sequence) the merge streams tens to
+// hundreds of MB, and what counts is the wavefronts in flight and the vector
+// instructions of a row: rows of up to kFewSlots or kSpec slots have variants
+// without the loop over further slots (22 and 33 VGPRs at D = 128 against 83: 8
+// wavefronts per SIMD instead of 5), and whatever is the same for a wavefront is
+// scalar (169 and 210 vector instructions).  Whole steps, one kernel for all
+// against these: 64 new tokens over 64 long contexts (131072 rows of 2 slots)
+// 616 -> 601 us, 4 over 188 (12032 rows of 6) 56.8 -> 55.8, 11 over 22 (9680 of
+// 6) 53.2 -> 52.3, 4 over 303 (19392 of 3) 44.5 -> 43.2.
 #include "pda_internal.h"
 
 namespace pda {
 namespace {
 
-// Maximum over the wavefront; every lane gets the same value.
+// Maximum over the wavefront's first LANES lanes (a power of two; the others hold
+// less); every lane gets the same value.
+template <int LANES>
 __device__ __forceinline__ float wave_max(float x) {
-  for (int o = 1; o < kWaveSize; o <<= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
+#pragma unroll
+  for (int o = 1; o < LANES; o <<= 1) x = fmaxf(x, __shfl_xor(x, o));
+  return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x)));
 }
 
-// Sum over the wavefront in a fixed butterfly order; every lane gets the same bits.
+// Sum over them in a fixed butterfly order (the others hold 0); every lane gets
+// the same bits.
+template <int LANES>
 __device__ __forceinline__ float wave_sum(float x) {
-  for (int o = 1; o < kWaveSize; o <<= 1) x += __shfl_xor(x, o);
-  return x;
+#pragma unroll
+  for (int o = 1; o < LANES; o <<= 1) x += __shfl_xor(x, o);
+  return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x)));
 }
 
 __device__ __forceinline__ int clamped_len(const StepArgs& a, int b) {
@@ -41,6 +57,7 @@ __device__ __forceinline__ int clamped_len(const StepArgs& a, int b) {
 }
 
 constexpr int kMergeRows = 4;  // rows (wavefronts) per workgroup
+constexpr int kFewSlots = 4;   // slots per row of the smallest variant
 constexpr int kSpec = 8;       // slots whose outputs are loaded before the length is known
 constexpr int kInFlight = 4;   // output loads in flight past them
 
@@ -48,12 +65,16 @@ constexpr int kInFlight = 4;   // output loads in flight past them
 // at slots row * S .. row * S + S - 1 (S = slots_per_row): first the prefix
 // partitions of its group, then, from slot row * S + Pp, its own partitions
 // (as many as the query chunk of new token i sees after the prefix).
-template <int D>
-__global__ void __launch_bounds__(kMergeRows * kWaveSize) __attribute__((amdgpu_waves_per_eu(5))) merge_kernel(const StepArgs a) {
+// SPEC slots are loaded early; MORE: a row may have more of them.
+template <int D, int SPEC, bool MORE>
+__global__ void __launch_bounds__(kMergeRows * kWaveSize) __attribute__((amdgpu_waves_per_eu(MORE ? 5 : 8)))
+merge_kernel(const StepArgs a) {
   constexpr int LPS = D / 4;             // lanes per slot: 4 columns each
   constexpr int SPI = kWaveSize / LPS;   // slots per load instruction
-  constexpr int NS = kSpec / SPI;
-  const int row = blockIdx.x * kMergeRows + (threadIdx.x >> 6);
+  constexpr int NS = SPEC / SPI;
+  constexpr int LANES = MORE ? kWaveSize : SPEC;  // lanes that hold a slot's state
+  // (the same for the whole wavefront: its divisions and addresses are scalar)
+  const int row = blockIdx.x * kMergeRows + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (kWaveSize - 1);
   if ((size_t)row >= (size_t)a.num_seqs * a.num_query_tokens * a.num_q_heads) return;  // spare wavefronts
   const int i = (row / a.num_q_heads) % a.num_query_tokens;
@@ -95,13 +116,14 @@ __global__ void __launch_bounds__(kMergeRows * kWaveSize) __attribute__((amdgpu_
     }
     if (!valid(s)) m = kNone, l = 0.f;
   };
+  const int state_end = MORE ? own_end : 1;  // (without MORE the first kWaveSize slots are all)
   float M = kNone;
-  for (int s0 = 0; s0 < own_end; s0 += kWaveSize) {
+  for (int s0 = 0; s0 < state_end; s0 += kWaveSize) {
     float m = kNone, l = 0.f;
     state(s0, m, l);
     M = fmaxf(M, m);
   }
-  M = wave_max(M);
+  M = wave_max<LANES>(M);
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
   float lpart = 0.f;
   auto add = [&](bool in, float wgt, const f32x4_t& v) {
@@ -110,7 +132,7 @@ __global__ void __launch_bounds__(kMergeRows * kWaveSize) __attribute__((amdgpu_
       for (int e = 0; e < 4; ++e) acc[e] = fmaf(wgt, v[e], acc[e]);
     }
   };
-  for (int s0 = 0; s0 < own_end; s0 += kWaveSize) {
+  for (int s0 = 0; s0 < state_end; s0 += kWaveSize) {
     float m = kNone, l = 0.f;
     state(s0, m, l);
     const float wgt = __builtin_amdgcn_exp2f(m - M);  // 2^(m - M), 0 for a slot that holds nothing
@@ -126,9 +148,9 @@ __global__ void __launch_bounds__(kMergeRows * kWaveSize) __attribute__((amdgpu_
         for (int i = 1; i < SPI; ++i) w_x = sub == i ? of_lane(x * SPI + i) : w_x;
         add(valid(x * SPI + sub), w_x, o_s[x]);
       }
-      x0 = kSpec;
+      x0 = SPEC;
     }
-    for (; x0 < end; x0 += kInFlight * SPI) {
+    for (; MORE && x0 < end; x0 += kInFlight * SPI) {
       f32x4_t v[kInFlight];
       auto slot = [&](int x) { return x0 + x * SPI + sub; };  // of these 64
       auto in = [&](int x) { return slot(x) < kWaveSize && valid(s0 + slot(x)); };
@@ -143,7 +165,7 @@ __global__ void __launch_bounds__(kMergeRows * kWaveSize) __attribute__((amdgpu_
   for (int o = LPS; o < kWaveSize; o <<= 1)
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
-  const float lsum = wave_sum(lpart);
+  const float lsum = wave_sum<LANES>(lpart);
   const bool pos = lsum > 0.f;  // 0: the row sees nothing
   if (sub == 0) {
     float* orow = a.out + (size_t)row * D + d0;
@@ -152,15 +174,26 @@ __global__ void __launch_bounds__(kMergeRows * kWaveSize) __attribute__((amdgpu_
   }
 }
 
+template <int D>
+void launch_d(const StepArgs& a, unsigned grid, hipStream_t stream) {
+  const dim3 threads(kMergeRows * kWaveSize);
+  if (a.slots_per_row <= kFewSlots)
+    hipLaunchKernelGGL((merge_kernel<D, kFewSlots, false>), dim3(grid), threads, 0, stream, a);
+  else if (a.slots_per_row <= kSpec)
+    hipLaunchKernelGGL((merge_kernel<D, kSpec, false>), dim3(grid), threads, 0, stream, a);
+  else
+    hipLaunchKernelGGL((merge_kernel<D, kSpec, true>), dim3(grid), threads, 0, stream, a);
+}
+
 }  // namespace
 
 hipError_t launch_merge(const StepArgs& a, int head_dim, hipStream_t stream) {
   const unsigned rows = (unsigned)a.num_seqs * (unsigned)a.num_query_tokens * (unsigned)a.num_q_heads;
   const unsigned grid = (rows + kMergeRows - 1) / kMergeRows;
   if (head_dim == 64)
-    hipLaunchKernelGGL(merge_kernel<64>, dim3(grid), dim3(kMergeRows * kWaveSize), 0, stream, a);
+    launch_d<64>(a, grid, stream);
   else if (head_dim == 128)
-    hipLaunchKernelGGL(merge_kernel<128>, dim3(grid), dim3(kMergeRows * kWaveSize), 0, stream, a);
+    launch_d<128>(a, grid, stream);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -1,5 +1,5 @@
 """GPU parity of the merge pass at the edges of its slot handling: slots
-per row around the 8 loaded ahead, the 64 states of a wavefront and the load
+per row around 4 and the 8 loaded ahead, the 64 states of a wavefront and the load
 rounds in between, at both head dims, without and with a shared prefix (whose
 slots come first and are followed by unused ones)."""
 import numpy as np
@@ -23,7 +23,7 @@ def dev():
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("parts", [2, 8, 9, 16, 17, 63, 64, 65, 72, 73, 129])
+@pytest.mark.parametrize("parts", [2, 4, 5, 8, 9, 16, 17, 63, 64, 65, 72, 73, 129])
 @pytest.mark.parametrize("prefix", [0, 1, 9, 70])
 def test_slot_edges(dev, D, parts, prefix):
     own = sorted({1, 2, parts // 2 + 1, parts - 1, parts})

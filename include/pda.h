@@ -266,15 +266,15 @@ int pda_append_kv(const pda_problem *prob, const void *k_new, const void *v_new,
 
 /* pda_append_kv followed by pda_decode, for one new token per sequence
  * (num_query_tokens 0 or 1; the KV-cache management and attention of one
- * rollout step, Section 3.2 and Appendix C).  When every pass-1 work item of
- * the step runs at once (a small batch, where each launch is a large part of
- * the step), or contexts are split into several partitions (so that few items
- * wait for the store), the append is folded into pass 1: the wavefront that reads
- * position L - 1 of a (sequence, KV head) first stores the new token's K and
- * V rows there, and the step needs no append launch.  Larger steps run the
- * append kernel first.  Arguments are those of pda_append_kv and pda_decode;
- * the caches and the output (bitwise those of the two calls) are written in
- * place.  PDA_ERR_UNSUPPORTED for num_query_tokens > 1. */
+ * rollout step, Section 3.2 and Appendix C).  In steps of up to 128 sequences
+ * whose pass-1 work items all run at once (a small batch, where each launch is a
+ * large part of the step) or whose contexts are split into 3 partitions or more,
+ * the append is folded into pass 1: a wavefront first stores the new K and V
+ * rows that go to the blocks it reads, whichever sequence they belong to, and
+ * the step needs no append launch.  Other steps run the append kernel first.
+ * Arguments are those of pda_append_kv and pda_decode; the caches and the output
+ * (bitwise those of the two calls, also where sequences share blocks and read
+ * each other's new rows) are written in place.  PDA_ERR_UNSUPPORTED for num_query_tokens > 1. */
 int pda_decode_append(const pda_problem *prob, const void *q, const void *k_new, const void *v_new,
                       void *k_cache, void *v_cache, const int32_t *block_table, const int32_t *context_lens,
                       float scale, float *out, void *workspace, size_t workspace_bytes, hipStream_t stream);
@@ -303,8 +303,8 @@ int pda_step_graph_launch(pda_step_graph *graph, hipStream_t stream);
  * same in every layer) computed once, in the first layer.  This is the
  * per-token loop a rollout engine replays (vLLM runs its decode steps as
  * captured graphs, Section 3.2): one graph launch stands for num_layers x 1-4
- * kernel launches (with one new token per sequence and a small batch, each
- * layer's append is folded into its pass 1, as in pda_decode_append).  Every layer has its own q, k_new, v_new, caches and out
+ * kernel launches (with one new token per sequence, each layer's append is
+ * folded into its pass 1 where pda_decode_append folds it).  Every layer has its own q, k_new, v_new, caches and out
  * (the layouts of pda_append_kv / pda_decode); the descriptor, block table,
  * lengths, scale and workspace are shared.  Launch and destroy the result
  * with pda_step_graph_launch / pda_step_graph_destroy; launches of one graph

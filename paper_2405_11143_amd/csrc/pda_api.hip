@@ -347,20 +347,26 @@ hipError_t launch_append_of(const pda_problem* p, const pda::StepArgs& args, con
                             static_cast<uint16_t*>(k_cache), static_cast<uint16_t*>(v_cache), p->head_dim, stream);
 }
 
-// Whether a step folds its KV append into pass 1: one new token per
-// sequence, and either every work item runs at once (a small batch, where the
-// append's own launch is a large part of the step: the 32-layer step of a
-// 4-sequence batch ran 1.6x faster as one graph with the appends folded), or
-// contexts are split so that at most one item in kFoldPartitions stores.  The
-// item's wavefront that stores the new rows waits for its stores before it
-// streams: where every item does (the Llama-3-8B step, one partition) that
-// cost 3% on MI355X, more than the separate append kernel (3.4 us); where one
-// in 22 does (8 contexts of up to 16384 tokens) the launch saved is 37.9 ->
-// 34.9 us, with 3-6 partitions 80.7 -> 79.0 (48 contexts of 4096) and 193 ->
-// 191.5 us (64 of 8192).
+// Whether a step folds its KV append into pass 1: one new token per sequence,
+// at most kFoldMaxSeqs sequences (every wavefront looks through all their new
+// rows, kept in registers), and either every work item runs at once or contexts
+// are split into kFoldPartitions or more.  The launch saved is about 2 us of the
+// step; what it costs is that the wavefronts that store a new row wait for it
+// before they stream, one in four of an item that ends a context.  Where
+// every item does and none of them can wait beside another (one partition, more
+// items than run at once: the Llama-3-8B step) that is 3%.  Folded / in two
+// launches on MI355X, 32 / 8 heads, contexts uniform up to the maximum, us: 6
+// sequences of 640 tokens 9.6 / 11.8, 96 of 1024 43.3 / 44.4, 96 of 256 14.4 /
+// 17.1; split contexts: 8 of 16384 (22 partitions) 51.7 / 53.8, 64 of 2048 55.3 /
+// 57.5, 48 of 4096 75.7 / 75.7, 64 of 8192 178.2 / 179.0, and planned for 8192
+// with contexts of up to 1024, where most items end one, 36.2 / 38.5; 32 of
+// 16384 181.3 / 176.9 (180.0 / 181.2 in other memory).  Two partitions: 64
+// sequences of 1024 with 16 KV heads 58.9 / 59.5; one: 64 of 2048 with 32
+// 184.2 / 182.7.
 constexpr int kFoldPartitions = 3;
 bool folds_append(const pda_problem* p, const Plan& plan) {
-  return query_tokens(p) == 1 && (plan.items <= (size_t)concurrent_items(plan) || plan.info.num_partitions >= kFoldPartitions);
+  return query_tokens(p) == 1 && p->num_seqs <= pda::kFoldMaxSeqs &&
+         (plan.items <= (size_t)concurrent_items(plan) || plan.info.num_partitions >= kFoldPartitions);
 }
 
 // Let pass 1 store the step's new K/V rows (one new token per sequence, no

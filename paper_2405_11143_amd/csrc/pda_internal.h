@@ -13,6 +13,7 @@ constexpr int kWaves = 4;         // wavefronts per partition workgroup
 constexpr int kMaxGroup = 16;     // query heads per KV head: one 16-row MFMA tile
 constexpr int kWideChunks = 2 * kWaves;  // query chunks of a work item with more than 4: two per wavefront
 constexpr int kWide16Chunks = 4 * kWaves;  // with more than 8: two workgroups of kWideChunks
+constexpr int kFoldMaxSeqs = 128;  // sequences of a step that folds its KV append into pass 1
 constexpr int kOrderThreads = 1024;  // the work-order kernel is one workgroup of this size
 constexpr int kOrderBuckets = 256;   // size classes of its counting sort (partition blocks, capped)
 
@@ -62,9 +63,9 @@ struct StepArgs {
   int32_t slots_per_row;            // Pp + P partial states per output row (P when no groups)
   int32_t num_regular_items;        // items below this index are (partition, sequence, KV head, chunk group)
   int32_t num_prefix_items;         // num_groups * Pp * RG * Hkv items after them
-  // The step's KV append folded into pass 1 (one new token per sequence, no
-  // shared-prefix groups), or null: the item that reads position L - 1 of
-  // (sequence, KV head) first stores that token's K and V rows there.
+  // The step's KV append folded into pass 1 (one new token per sequence, at
+  // most kFoldMaxSeqs sequences, no shared-prefix groups), or null: a wavefront
+  // first stores the new rows that go to the blocks it reads.
   const uint16_t* k_new;            // bf16 [B][Hkv][D]
   const uint16_t* v_new;            // bf16 [B][Hkv][D]
   uint16_t* k_store;                // the K cache (a.k, writable)

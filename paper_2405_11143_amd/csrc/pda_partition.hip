@@ -81,7 +81,8 @@ struct Staging {
 
 // Which paths a launch compiles.  A launch whose items all have one tile
 // (every decode step without shared-prefix groups) compiles the register
-// path only (139 VGPRs at D = 128, 33 KiB of LDS); with up to 4 query chunks
+// path only (138 VGPRs at D = 128, 33 KiB of LDS; with a folded append 141, or
+// 144 for more than 64 sequences); with up to 4 query chunks
 // per item both paths are compiled (167 VGPRs, 50.5 KiB); with more, which
 // comes here only with shared-prefix groups, the wide variant also folds two
 // tiles per wavefront (241 VGPRs, 2 workgroups per compute unit).
@@ -379,35 +380,104 @@ __device__ void run_staged(WaveAttention<D>& wave, WaveAttention<D>& wave_b, Sta
   __syncthreads();  // the staging area is reused by the epilogue
 }
 
-// The step's KV append folded into pass 1 (one new token per sequence, no
-// shared-prefix groups): the wavefront whose run of blocks holds position t
-// = L - 1 of (sequence b, KV head g) stores the new token's K and V rows
-// there, and waits for the stores to complete, before it loads any tile.  No
-// other wavefront or item reads that block (the last of the sequence's own
-// context), and the wavefront's later loads of it miss its compute unit's
-// L1 (stores do not allocate there), so they see the new rows.  A block id
-// outside the pool is skipped, as the separate append does.
+// The step's KV append folded into pass 1 (one new token per sequence, at most
+// kFoldMaxSeqs sequences, no shared-prefix groups): before a wavefront loads any tile, it
+// stores every new row that goes to a block of its run, and waits for those
+// stores.  Mostly that is its own sequence's, in the run that ends the context.
+// But sequences may share blocks -- several rows of one context with lengths
+// L, L + 1, ..., each appending its own token, say -- and then a wavefront reads
+// rows that other workgroups store in this launch.  Nothing orders the two, so
+// it stores those rows itself: every writer of a slot writes the same bytes,
+// and the wavefront's later loads miss its compute unit's L1 (stores do not
+// allocate there), so they see them.  The wavefront's own row is stored first:
+// the search for the others runs while it waits for that store.
+
+// The lane's 16-byte piece of sequence b's new row of KV head g (lanes below
+// D / 8: K, the next D / 8: V), and its place in slot `slot` of block `phys`.
 template <int D>
-__device__ __forceinline__ void store_new_token(const StepArgs& a, int b, int g, int t, const int32_t* table_row,
-                                                int lane) {
-  constexpr int CPR = D / 8;  // 16-byte pieces per row
-  const int phys = table_row[t / kBlockTokens];
-  if ((unsigned)phys < (unsigned)a.num_blocks && lane < 2 * CPR) {
-    const int c = lane % CPR;
-    const size_t src = ((size_t)b * a.num_kv_heads + g) * CPR + c;
-    const size_t tile = (size_t)phys * a.num_kv_heads + g;
-    const int o = t % kBlockTokens;
-    if (lane < CPR)
-      reinterpret_cast<uint4*>(a.k_store)[(tile * CPR + c) * kBlockTokens + o] =
-          reinterpret_cast<const uint4*>(a.k_new)[src];
-    else
-      reinterpret_cast<uint4*>(a.v_store)[(tile * kBlockTokens + o) * CPR + c] =
-          reinterpret_cast<const uint4*>(a.v_new)[src];
-  }
-  __builtin_amdgcn_s_waitcnt(0);  // every memory operation of the wavefront has completed
+__device__ __forceinline__ uint4 load_new_row(const StepArgs& a, int b, int g, int lane) {
+  constexpr int CPR = D / 8;
+  const size_t src = ((size_t)b * a.num_kv_heads + g) * CPR + lane % CPR;
+  return reinterpret_cast<const uint4*>(lane < CPR ? a.k_new : a.v_new)[src];
+}
+template <int D>
+__device__ __forceinline__ void store_new_row(const StepArgs& a, const uint4& piece, int g, int phys, int slot, int lane) {
+  constexpr int CPR = D / 8;
+  const int c = lane % CPR;
+  const size_t tile = (size_t)phys * a.num_kv_heads + g;
+  if (lane < CPR)
+    reinterpret_cast<uint4*>(a.k_store)[(tile * CPR + c) * kBlockTokens + slot] = piece;
+  else if (lane < 2 * CPR)
+    reinterpret_cast<uint4*>(a.v_store)[(tile * kBlockTokens + slot) * CPR + c] = piece;
 }
 
-template <int D, int MODE>
+// Lane x, set k: length of sequence 64 k + x and the block its new token goes to
+// (none for an empty context, or an id outside the pool: the separate append
+// skips those too).  Only loaded here, looked at where they are needed: the
+// loads run beside the wavefront's own block ids and query rows.
+template <int SETS>
+struct NewRows {
+  int len[SETS], to[SETS];
+  uint4 own;  // the lane's piece of the wavefront's own sequence's new row
+  // The length of sequence b.
+  __device__ __forceinline__ int load_lengths(const StepArgs& a, int b, int lane) {
+#pragma unroll
+    for (int k = 0; k < SETS; ++k)
+      if (k == 0 || k * kWaveSize < a.num_seqs) len[k] = a.lens[min(k * kWaveSize + lane, a.num_seqs - 1)];
+    int L = __builtin_amdgcn_readlane(len[0], b % kWaveSize);
+#pragma unroll
+    for (int k = 1; k < SETS; ++k)
+      if (b >= k * kWaveSize) L = __builtin_amdgcn_readlane(len[k], b % kWaveSize);
+    return L;
+  }
+  template <int D>
+  __device__ __forceinline__ void load_blocks(const StepArgs& a, int b, int g, int lane) {
+#pragma unroll
+    for (int k = 0; k < SETS; ++k)
+      if (k == 0 || k * kWaveSize < a.num_seqs)
+        to[k] = a.table[(size_t)min(k * kWaveSize + lane, a.num_seqs - 1) * a.max_blocks_per_seq +
+                        position(a, k) / kBlockTokens];
+    own = load_new_row<D>(a, b, g, lane);
+  }
+  __device__ __forceinline__ int position(const StepArgs& a, int k) const {
+    return max(min(len[k], a.max_context_len), 1) - 1;
+  }
+  __device__ __forceinline__ bool has(const StepArgs& a, int k, int lane) const {
+    return k * kWaveSize + lane < a.num_seqs && len[k] > 0 && a.max_context_len > 0 &&
+           (unsigned)to[k] < (unsigned)a.num_blocks;
+  }
+};
+
+// The other sequences' rows that go to blocks [j0, j1) of table_row (ids: the
+// first 64 of them, one per lane, -1 past the end).  True if there are any.
+template <int D, int SETS>
+__device__ __forceinline__ bool store_other_rows(const StepArgs& a, const NewRows<SETS>& nr, int b, int g,
+                                                 const int32_t* table_row, int ids, int j0, int j1, int lane) {
+  bool any = false;
+#pragma unroll
+  for (int k = 0; k < SETS; ++k) {
+    if (k > 0 && k * kWaveSize >= a.num_seqs) break;
+    bool match = false;
+    auto scan = [&](int window, int cn) {
+      for (int i = 0; i < cn; i += 8)
+#pragma unroll
+        for (int x = 0; x < 8; ++x) match |= nr.to[k] == __builtin_amdgcn_readlane(window, i + x);
+    };
+    scan(ids, min(kWaveSize, j1 - j0));
+    for (int c0 = j0 + kWaveSize; c0 < j1; c0 += kWaveSize)
+      scan(c0 + lane < j1 ? table_row[c0 + lane] : -1, min(kWaveSize, j1 - c0));
+    uint64_t hits = __builtin_amdgcn_ballot_w64(match && nr.has(a, k, lane) && k * kWaveSize + lane != b);
+    any |= hits != 0;
+    for (; hits != 0; hits &= hits - 1) {
+      const int x = __builtin_ctzll(hits);
+      store_new_row<D>(a, load_new_row<D>(a, k * kWaveSize + x, g, lane), g, __builtin_amdgcn_readlane(nr.to[k], x),
+                       __builtin_amdgcn_readlane(nr.position(a, k), x) % kBlockTokens, lane);
+    }
+  }
+  return any;
+}
+
+template <int D, int MODE, int SETS>
 __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, int b, int p) {
   PassShared<D>& sh = lds.sh;
   using WA = WaveAttention<D>;
@@ -431,7 +501,12 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, i
   const int tile = w % ntile;
   const int slice = w / ntile;
 
-  int L = a.lens[b];
+  NewRows<SETS == 0 ? 1 : SETS> nr;
+  int L;
+  if constexpr (SETS > 0)
+    L = nr.load_lengths(a, b, lane);
+  else
+    L = a.lens[b];
   L = L < 0 ? 0 : (L > a.max_context_len ? a.max_context_len : L);
   const int Tp = a.partition_tokens;
   const int t0_all = seq_prefix_len(a, b);  // tokens before it belong to the group's prefix items
@@ -458,6 +533,7 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, i
     }
   }
   if (p >= nparts_max) return;
+  if constexpr (SETS > 0) nr.template load_blocks<D>(a, b, g, lane);
 
   const char* kpool = reinterpret_cast<const char*>(a.k) + (size_t)g * WA::kTileBytes;
   const char* vpool = reinterpret_cast<const char*>(a.v) + (size_t)g * WA::kTileBytes;
@@ -579,9 +655,30 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, i
     const int per_slice = (j_end - j_begin + kWaves - 1) / kWaves;
     const int wj0 = min(j_end, j_begin + w * per_slice);
     const int wj1 = min(j_end, wj0 + per_slice);
-    if (a.k_new && L > 0 && wj0 <= (L - 1) / kBlockTokens && (L - 1) / kBlockTokens < wj1)  // wavefront-uniform
-      store_new_token<D>(a, b, g, L - 1, table_row, lane);
-    wave.run(table_row, wj0, wj1, L, ca.l_first, max(ca.l_vis, 0), kpool, vpool, block_bytes, a.num_blocks);
+    int ids = wj0 + lane < wj1 ? table_row[wj0 + lane] : -1;
+    bool own = false;  // the run holds the sequence's own new row
+    if constexpr (SETS > 0) {
+      // (all loaded here, so that nothing below waits for the store)
+      asm volatile("" : "+v"(ids));
+#pragma unroll
+      for (int k = 0; k < SETS; ++k)
+        if (k == 0 || k * kWaveSize < a.num_seqs) asm volatile("" : "+v"(nr.to[k]));
+      const int j_own = (L - 1) / kBlockTokens;
+      own = L > 0 && wj0 <= j_own && j_own < wj1;
+      if (own) {
+        const int phys = j_own - wj0 < kWaveSize ? __builtin_amdgcn_readlane(ids, j_own - wj0) : table_row[j_own];
+        if ((unsigned)phys < (unsigned)a.num_blocks) store_new_row<D>(a, nr.own, g, phys, (L - 1) % kBlockTokens, lane);
+      }
+    }
+    wave.run(table_row, ids, wj0, wj1, L, ca.l_first, max(ca.l_vis, 0), kpool, vpool, block_bytes, a.num_blocks, !own,
+             [&]() {
+               if constexpr (SETS > 0) {
+                 const bool stored = store_other_rows<D>(a, nr, b, g, table_row, ids, wj0, wj1, lane) || own;
+                 if (stored) __builtin_amdgcn_s_waitcnt(0);  // every memory operation of the wavefront has completed
+                 return stored;
+               }
+               return false;
+             });
   } else if constexpr (MODE != kModeRegister) {  // several tiles: every block staged once through LDS for all of them
     int J1 = j_begin;
     for (int t = 0; t < nchunk; ++t) {
@@ -677,7 +774,9 @@ __device__ void prefix_item(const StepArgs& a, PassLds<D, MODE>& lds, int pitem)
     const int per_slice = (j_end - j_begin + kWaves - 1) / kWaves;
     const int wj0 = min(j_end, j_begin + w * per_slice);
     const int wj1 = min(j_end, wj0 + per_slice);
-    wave.run(table_row, wj0, wj1, plen, l_first, plen, kpool, vpool, block_bytes, a.num_blocks);
+    const int ids = wj0 + lane < wj1 ? table_row[wj0 + lane] : 0;
+    wave.run(table_row, ids, wj0, wj1, plen, l_first, plen, kpool, vpool, block_bytes, a.num_blocks, true,
+             [] { return false; });
   } else if constexpr (MODE != kModeRegister) {  // several tiles: every block staged once through LDS for all of them
     run_staged<D, kStepBlocks, 1>(wave, wave, lds.st, table_row, j_begin, j_end, j_end, 0, slice < slices, slice,
                                   slices, plen, l_first, plen, 0, 0, kpool, vpool, block_bytes, a.num_blocks);
@@ -704,14 +803,15 @@ __device__ void prefix_item(const StepArgs& a, PassLds<D, MODE>& lds, int pitem)
 }
 
 // Occupancy: 3 wavefronts per SIMD (12 per compute unit) at most 168 VGPRs;
-// the wide variant 2 (256 VGPRs).
-template <int D, int MODE>
+// the wide variant 2 (256 VGPRs).  SETS: sets of 64 sequences of a folded append
+// (0: the step appends nothing, or before).
+template <int D, int MODE, int SETS = 0>
 __global__ void __launch_bounds__(kWaves * kWaveSize)
 __attribute__((amdgpu_waves_per_eu(MODE == kModeWide ? 2 : 3)))
 partition_kernel(const StepArgs a) {
   __shared__ __align__(16) PassLds<D, MODE> lds;
   if (!a.order) {  // every item runs at once: a workgroup's place in the grid is its item (no divisions)
-    regular_item<D, MODE>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
+    regular_item<D, MODE, SETS>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
     return;
   }
   const int item = a.order[blockIdx.x];
@@ -719,8 +819,8 @@ partition_kernel(const StepArgs a) {
   if ((unsigned)item >= (unsigned)(a.num_regular_items + a.num_prefix_items)) return;
   if (item < a.num_regular_items) {  // item = (p * B + b) * HC + gc
     const int HC = a.num_kv_heads * a.num_chunk_groups;
-    regular_item<D, MODE>(a, lds, item % HC, (item / HC) % a.num_seqs, item / (HC * a.num_seqs));
-  } else {
+    regular_item<D, MODE, SETS>(a, lds, item % HC, (item / HC) % a.num_seqs, item / (HC * a.num_seqs));
+  } else if constexpr (SETS == 0) {
     prefix_item<D, MODE>(a, lds, item - a.num_regular_items);
   }
 }
@@ -741,6 +841,10 @@ hipError_t launch_d(const StepArgs& a, hipStream_t stream) {
   const dim3 block(kWaves * kWaveSize);
   if (a.chunks_per_group > kWaves)
     hipLaunchKernelGGL((partition_kernel<D, kModeWide>), grid, block, 0, stream, a);
+  else if (a.k_new && a.num_seqs <= kWaveSize)
+    hipLaunchKernelGGL((partition_kernel<D, kModeRegister, 1>), grid, block, 0, stream, a);
+  else if (a.k_new)
+    hipLaunchKernelGGL((partition_kernel<D, kModeRegister, kFoldMaxSeqs / kWaveSize>), grid, block, 0, stream, a);
   else if (one && !several)
     hipLaunchKernelGGL((partition_kernel<D, kModeRegister>), grid, block, 0, stream, a);
   else

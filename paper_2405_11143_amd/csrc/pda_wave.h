@@ -379,18 +379,25 @@ struct WaveAttention {
   // outstanding loads exactly and waits only for the tiles it is about to
   // use; the scheduling barriers keep each prefetch ahead of the first use of
   // the current tiles.  Past the end of the run the prefetch gets a
-  // zero-length descriptor.  Block ids come 64 at a time, one per lane, and
-  // are read with readlane, so no tile load waits on a scalar load.
-  __device__ __forceinline__ void run(const int32_t* table_row, int j0, int j1, int L, int l_first, int l_vis,
-                                      const char* kpool, const char* vpool, size_t block_bytes, int num_blocks) {
+  // zero-length descriptor.  Block ids come 64 at a time, one per lane (the
+  // first 64 in `ids`), and are read with readlane, so no tile load waits on a
+  // scalar load.
+  //
+  // `first`: load the first block's tiles before `again` runs; when that
+  // returns true (wavefront-uniform) they are loaded after it.
+  template <class Again>
+  __device__ __forceinline__ void run(const int32_t* table_row, int ids, int j0, int j1, int L, int l_first, int l_vis,
+                                      const char* kpool, const char* vpool, size_t block_bytes, int num_blocks,
+                                      bool first, Again&& again) {
     const int cnt = j1 - j0;
     uint4 k0[NC], v0[4], k1[NC], v1[4];
     for (int c0 = 0; c0 < cnt; c0 += kWaveSize) {
       const int cn = min(kWaveSize, cnt - c0);
       const int jc = j0 + c0;
-      const int ids = lane < cn ? table_row[jc + lane] : 0;
+      if (c0 > 0) ids = lane < cn ? table_row[jc + lane] : 0;
       auto id = [&](int i) { return __builtin_amdgcn_readlane(ids, i); };
-      load_tiles(k0, v0, kpool, vpool, block_bytes, num_blocks, id(0), true);
+      load_tiles(k0, v0, kpool, vpool, block_bytes, num_blocks, id(0), c0 > 0 || first);
+      if (c0 == 0 && again()) load_tiles(k0, v0, kpool, vpool, block_bytes, num_blocks, id(0), true);
       for (int i = 0; i < cn; i += 2) {
         load_tiles(k1, v1, kpool, vpool, block_bytes, num_blocks, id(min(i + 1, cn - 1)), i + 1 < cn);
         __builtin_amdgcn_sched_barrier(0);

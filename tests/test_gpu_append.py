@@ -172,27 +172,30 @@ def test_model_step_graph_replays(dev, case):
         graph.close()
 
 
-@pytest.mark.parametrize("case", ["edge", "split_small", "split_large", "llama3_8b"])
+@pytest.mark.parametrize("case", ["edge", "split_small", "split_large", "two_partitions", "llama3_8b"])
 def test_decode_append_matches_two_calls(dev, case):
     """pda_decode_append against pda_append_kv + pda_decode on copies of the
-    same caches: caches and outputs bitwise equal.  Small steps (every work
-    item at once) fold the append into pass 1: empty and negative lengths, a
-    new token that opens a block, a sequence whose new token's block id is
-    outside the pool (its append is skipped, its rows are NaN in both), split
-    contexts.  Larger steps (split_large, the full Llama-3-8B step) run the
-    append kernel first."""
+    same caches: caches and outputs bitwise equal.  Steps whose work items all
+    run at once fold the append into pass 1: empty and negative lengths, a new
+    token that opens a block, a sequence whose new token's block id is outside
+    the pool (its append is skipped, its rows are NaN in both), split contexts.
+    So do larger steps of 3 partitions or more (split_large); with two
+    partitions, and in the full Llama-3-8B step, the append kernel runs first."""
     if case == "llama3_8b":
         st, tp = W.make_structure("llama3_8b"), 0
     else:
         lens = {"edge": [0, 1, 16, 17, 33, -2, 700, 1000, 2049],
                 "split_small": [1, 17, 64, 65, 300, 499, 500, 128],
-                "split_large": [int(x) for x in np.random.default_rng(5).integers(1, 900, 40)]}[case]
+                "split_large": [int(x) for x in np.random.default_rng(5).integers(1, 900, 40)],
+                "two_partitions": [int(x) for x in np.random.default_rng(6).integers(1, 900, 60)]}[case]
         st = W.custom_structure(len(lens), 32, 8, 128, lens, seed=91)
-        tp = 0 if case == "edge" else 64
+        tp = {"edge": 0, "two_partitions": 512}.get(case, 64)
     plan = pda_plan(make_problem(st.B, st.Hq, st.Hkv, st.D, st.num_blocks, st.max_blocks_per_seq,
                                  st.max_context_len, tp))
     items = st.B * st.Hkv * plan["num_partitions"]
-    print(f"decode_append {case}: {items} work items ({'folded' if items <= 768 else 'append kernel first'})")
+    folded = st.B <= 128 and (items <= 768 or plan["num_partitions"] >= 3)
+    assert folded == (case not in ("two_partitions", "llama3_8b"))
+    print(f"decode_append {case}: {items} work items ({'folded' if folded else 'append kernel first'})")
     q, k, v = W.fill_values(st, dev, fill="nan")
     kn, vn = W.fill_new_kv(st, 1, dev)
     table = st.block_table.copy()
@@ -213,3 +216,46 @@ def test_decode_append_matches_two_calls(dev, case):
     assert torch.equal(torch.nan_to_num(got), torch.nan_to_num(ref)), "output"
     if case == "edge":
         assert torch.isnan(got[6]).all() and not torch.isnan(got[7]).any()
+
+
+# rows of one context scored together: (contexts, rows per context, context length, Hq, Hkv, D, partition_tokens)
+SHARED_CASES = {
+    "whole": (2, 6, 201, 8, 2, 64, 0),              # every item at once, runs of a few blocks
+    "split": (2, 4, 700, 32, 8, 128, 256),          # 3 partitions, every item at once
+    "many": (24, 5, 333, 32, 8, 128, 112),          # 3 partitions, 120 rows, 2880 items
+    "two_partitions": (24, 5, 333, 32, 8, 128, 176),  # 1920 items, 2 partitions
+    "over_128": (40, 4, 333, 32, 8, 128, 112),       # more sequences than a folded append looks through
+    "long": (2, 5, 16 * 300 + 2, 16, 1, 128, 4864),   # runs of more than 64 blocks, new rows of two blocks
+}
+
+
+@pytest.mark.parametrize("case", sorted(SHARED_CASES))
+def test_decode_append_with_shared_blocks(dev, case):
+    """Sequences of one batch that share blocks and read each other's new
+    rows: several rows of one context with lengths L, L + 1, ... over the same
+    block table, each appending its own token, and a sequence whose second
+    block is the one another context's new rows go to.  Caches and outputs are
+    bitwise those of pda_append_kv + pda_decode, whichever way the step takes."""
+    contexts, rows, length, Hq, Hkv, D, tp = SHARED_CASES[case]
+    st = W.custom_structure(contexts + 1, Hq, Hkv, D, [length] * contexts + [60], seed=92)
+    table = np.repeat(st.block_table, [rows] * contexts + [1], axis=0)
+    table[-1, 1] = st.block_table[0, (length - 1) // 16]
+    lens = np.array([length - rows + 1 + i for _ in range(contexts) for i in range(rows)] + [60], np.int32)
+    B = len(lens)
+    bt, ln = torch.from_numpy(np.ascontiguousarray(table)).to(dev), torch.from_numpy(lens).to(dev)
+    _, k, v = W.fill_values(st, dev, fill="zero")
+    kw = dict(max_context_len=st.max_context_len, partition_tokens=tp)
+    for step in range(4):
+        q = W.normal_draw((B, 1, Hq, D), 930 + step, 0, dev).to(torch.bfloat16)
+        kn = W.normal_draw((B, 1, Hkv, D), 930 + step, 1, dev).to(torch.bfloat16)
+        vn = W.normal_draw((B, 1, Hkv, D), 930 + step, 2, dev).to(torch.bfloat16)
+        k2, v2 = k.clone(), v.clone()
+        pda_append_kv(kn, vn, bt, ln, k, v, max_context_len=st.max_context_len, num_q_heads=Hq)
+        ref = pda_decode(q, k, v, bt, ln, st.scale, **kw)
+        got = pda_decode_append(q, kn, vn, k2, v2, bt, ln, st.scale, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(k.view(torch.int16), k2.view(torch.int16)), (step, "K cache")
+        assert torch.equal(v.view(torch.int16), v2.view(torch.int16)), (step, "V cache")
+        assert torch.equal(got, ref), (step, "output")
+    want = oracle.decode_multi(bits16(q), bits16(k), bits16(v), table, lens, st.scale, threads=16)
+    check(got.cpu().numpy(), want, f"decode_append with shared blocks, {case}")

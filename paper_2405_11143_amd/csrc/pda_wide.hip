@@ -44,6 +44,7 @@ constexpr int kWgChunks = 2 * kWaves;  // chunks of a workgroup
 constexpr int kStageBlocks = 2;        // blocks of a staged step: 32 tokens
 constexpr int kBuffers = 4;            // one step folded, three in flight
 constexpr int kWindow = 1024;          // block ids held in LDS at a time
+constexpr float kExactMax = 128.f;     // running maxima whose rounding is below P's resolution
 
 template <int D>
 struct WideLds {
@@ -143,7 +144,7 @@ wide_kernel(const StepArgs a) {
 
   float scale = a.scale_log2;
   const unsigned flip = scale < 0.f ? 0x80008000u : 0u;
-  const unsigned keep = fabsf(scale) < 1.2e-38f ? 0u : 0xffffffffu;  // a zero scale: zero scores, whatever is masked
+  const unsigned keep = scale == 0.f ? 0u : 0xffffffffu;  // a zero scale: zero scores, whatever is masked
   scale = keep ? fabsf(scale) : 1.f;
   bf16x8_t q[KS];
   {
@@ -160,7 +161,14 @@ wide_kernel(const StepArgs a) {
   for (int t = 0; t < VT; ++t)
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[t][i] = 0.f;
-  float m_run = -1e30f, l_run = 0.f;
+  // The running maximum before scaling, and scaled and rounded.  A step that
+  // moves the maximum takes its probabilities as exp2((s - m_raw) * scale): the
+  // row's largest score gets exactly 1, so a row that sees one token returns its
+  // V row bit for bit, and scores of any size cancel.  The other steps take them
+  // as exp2(s * scale - m_run), in one instruction less per score, as long as
+  // the rounding of m_run (up to kExactMax: below 2^-17, the resolution of P) is
+  // all that the two differ by.
+  float m_raw = fmaxf(-1e30f / scale, -__FLT_MAX__), m_run = mul_rounded(m_raw, scale), l_run = 0.f;
 
   const char* kpool = reinterpret_cast<const char*>(a.k) + (size_t)g * kTileBytes;
   const char* vpool = reinterpret_cast<const char*>(a.v) + (size_t)g * kTileBytes;
@@ -209,7 +217,7 @@ wide_kernel(const StepArgs a) {
   for (int t = 0; t < VT; ++t) tr_off[t] = tr_row + 32 * (t ^ (D == 128 ? s16 / 4 : s16 / 8));
 
   f32x16_t s;  // scores of the step to fold: reg i is token tok0 + 8 (i / 4) + 4 hh + i % 4
-  float top;   // the largest of them, scaled
+  float top;   // the largest of them
   auto scores = [&](const uint4* blocks) {
     f32x16_t x;
 #pragma unroll
@@ -223,7 +231,7 @@ wide_kernel(const StepArgs a) {
     float x = max3(s[0], s[1], s[2]);
 #pragma unroll
     for (int i = 3; i + 1 < 15; i += 2) x = max3(x, s[i], s[i + 1]);
-    top = max3(x, s[15], s[15]) * scale;
+    top = max3(x, s[15], s[15]);
     asm volatile("" : "+v"(top));  // the MFMA results are first read in their own basic block
   };
   auto mask = [&](int tok0) {
@@ -238,12 +246,12 @@ wide_kernel(const StepArgs a) {
   };
   // o += p V of the tokens [l_vis_a, l_vis) of a step, one after the other,
   // for the second chunk's rows (never reached with finite values).
-  auto add_apart = [&](int tok0, const uint4* blocks) {
+  auto add_apart = [&](int tok0, const uint4* blocks, float ref) {
     for (int x = max(tok0, l_vis_a) - tok0; x < min(32, l_vis - tok0); ++x) {
       float sx = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) sx = i == 4 * (x / 8) + x % 4 ? s[i] : sx;
-      const float mine = exp2_fast(fmaf(sx, scale, -m_run));
+      const float mine = exp2_fast(fmaf(sx, scale, -ref));
       const float other = __shfl_xor(mine, 32);
       const float px = (x / 4) % 2 == hh ? mine : other;
       const int perm = D == 128 ? 4 * (x & 3) : 4 * ((x >> 1) & 1);
@@ -297,23 +305,27 @@ wide_kernel(const StepArgs a) {
           vf[m][t] = make_uint4(word(vf[m][t].x, 16 * m), word(vf[m][t].y, 16 * m + 2), word(vf[m][t].z, 16 * m + 8),
                                 word(vf[m][t].w, 16 * m + 10));
     }
-    if (__builtin_amdgcn_ballot_w64(top > m_run + 8.f) != 0) {
-      const float mx = fmaxf(top, __shfl_xor(top, 32));
-      const float mn = fmaxf(m_run, mx);
-      const float al = exp2_fast(m_run - mn);
-      m_run = mn;
+    float ref = m_run;
+    if (__builtin_amdgcn_ballot_w64(fmaf(top, scale, -m_run) > 8.f || fabsf(m_run) > kExactMax) != 0) {
+      const float mn = fmaxf(m_raw, fmaxf(top, __shfl_xor(top, 32)));
+      const float al = exp2_fast((m_raw - mn) * scale);
+      m_raw = mn;
+      m_run = mul_rounded(mn, scale);
+      ref = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] -= m_raw;
       l_run *= al;
 #pragma unroll
       for (int t = 0; t < VT; ++t) o[t] *= al;
     }
-    if (apart) add_apart(tok0, blocks);
+    if (apart) add_apart(tok0, blocks, ref);
     const f32x16_t ns = scores(next_blocks);
     bf16x8_t bh[2], bl[2];
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
       float pr[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) pr[i] = exp2_fast(fmaf(s[8 * m + i], scale, -m_run));
+      for (int i = 0; i < 8; ++i) pr[i] = exp2_fast(fmaf(s[8 * m + i], scale, -ref));
       l_run += ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
       unsigned hw[4], lw[4];
 #pragma unroll

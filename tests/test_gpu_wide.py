@@ -80,3 +80,68 @@ def test_non_finite_new_rows_stay_with_their_chunk(dev, D, value, partition_toke
         assert not np.isfinite(got[b, x:, 4:, 37]).any(), (b, x)
         got[b, first:, 4:, 37] = ref[b, first:, 4:, 37]
     check(got, ref, f"non-finite new rows D={D} Tp={partition_tokens}")
+
+
+def rows_of(st, cache_rows, b, g, n):
+    """The first n K or V rows of (sequence, KV head) as float64."""
+    t = np.arange(n)
+    return cache_rows[st.block_table[b, t // 16], g, t % 16].astype(np.float64)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("factor", [1.0, 25.0, -3.0])
+@pytest.mark.parametrize("n,partition_tokens", [(17, 0), (40, 0), (40, 16), (100, 0)])
+def test_one_token_rows_return_v(dev, D, factor, n, partition_tokens):
+    """The row that sees one token gives it probability exactly 1 and returns
+    its V row bit for bit, as the first row of every fresh prompt does."""
+    Hq, Hkv, lens = 8, 2, [n, n - 3, 1, n - 1]
+    st = W.custom_structure(len(lens), Hq, Hkv, D, lens, seed=900 + n)
+    _, k, v = W.fill_values(st, dev, fill="nan")
+    q = W.fill_multi_q(st, n, dev)
+    bt, ln = torch.from_numpy(st.block_table).to(dev), torch.from_numpy(st.context_lens).to(dev)
+    got = pda_decode(q, k, v, bt, ln, st.scale * factor, max_context_len=st.max_context_len,
+                     partition_tokens=partition_tokens).cpu().numpy()
+    vh = v.float().cpu().numpy()
+    for b, L in enumerate(lens):
+        for h in range(Hq):
+            assert np.array_equal(got[b, n - L, h], vh[st.block_table[b, 0], h * Hkv // Hq, 0]), (b, h)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("exponent", [5, 17], ids=["2^10", "2^34"])
+@pytest.mark.parametrize("partition_tokens", [0, 48])
+def test_large_scores(dev, D, exponent, partition_tokens):
+    """Finite q and K of a size whose scaled scores reach 2^14 and 2^34: the
+    softmax is all on one token, and the rows are that token's V row within
+    2^-15 of it (a running maximum may stay up to 2^8 below, and then the
+    token's probability is kept in two bf16 halves, to 2^-16).  Rows whose two largest scores differ by less than the rounding of two
+    fp32 dot products (D terms, each within 2^-24 of the sum of magnitudes) and
+    of two running maxima, plus 64 powers of two, are left out."""
+    n, Hq, Hkv = 40, 8, 2
+    lens = [n, n + 41, 300, 17]
+    st = W.custom_structure(len(lens), Hq, Hkv, D, lens, seed=950)
+    _, k, v = W.fill_values(st, dev, fill="zero")
+    q = W.fill_multi_q(st, n, dev) * 2.0 ** exponent
+    k = k * 2.0 ** exponent
+    got = run(st, q, k, v, dev, partition_tokens)
+    assert np.isfinite(got).all()
+    kr = W.k_cache_to_rows(k).float().cpu().numpy()
+    vh, qh = v.float().cpu().numpy(), q.float().cpu().numpy().astype(np.float64)
+    scale_log2 = st.scale * np.log2(np.e)
+    checked = total = 0
+    for b, L in enumerate(lens):
+        for h in range(Hq):
+            K, V = rows_of(st, kr, b, h * Hkv // Hq, L), rows_of(st, vh, b, h * Hkv // Hq, L)
+            s = qh[b, :, h] @ K.T * scale_log2
+            size = np.abs(qh[b, :, h]) @ np.abs(K.T) * scale_log2
+            for i in range(max(0, n - L), n):
+                vis = L - n + 1 + i
+                best, second = np.argsort(-s[i, :vis])[[0, min(1, vis - 1)]]
+                bound = 2 * D * 2.0 ** -24 * size[i, :vis].max() + 2 * 2.0 ** -24 * np.abs(s[i, :vis]).max() + 64
+                total += 1
+                if vis > 1 and s[i, best] - s[i, second] < bound:
+                    continue
+                checked += 1
+                assert (np.abs(got[b, i, h] - V[best]) <= 2.0 ** -15 * np.abs(V[best])).all(), (b, i, h)
+    print(f"large scores 2^{exponent}: {checked} of {total} rows", flush=True)
+    assert checked > total // 2

@@ -57,11 +57,21 @@ struct WideLds {
   int ids[kWindow];
 };
 
-// 16 bytes per lane from base + offset straight into LDS at lds_base + 16 lane.
-// The compiler does not count this load: the caller waits with wait_loads.
-__device__ __forceinline__ void load_to_lds(const char* base, int offset, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_base)
-               : "memory", "m0");
+// 16 bytes per lane from k + k_off and v + v_off straight into LDS, at k_lds and
+// v_lds plus 16 lane.  The compiler does not count these loads: the caller waits
+// with wait_loads.  (It counts the builtin's, and waits for all of them before
+// every LDS read: no load would stay in flight.)  M0, which names the LDS
+// address, belongs to the compiler: it gets back what it held.
+__device__ __forceinline__ void load_to_lds(const char* k, int k_off, unsigned k_lds, const char* v, int v_off,
+                                            unsigned v_lds) {
+  unsigned m0;
+  asm volatile("s_mov_b32 %0, m0\n\t"
+               "s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
+               "s_mov_b32 m0, %6\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\t"
+               "s_mov_b32 m0, %0"
+               : "=&s"(m0)
+               : "v"(k_off), "v"(v_off), "s"(k), "s"(v), "s"(k_lds), "s"(v_lds)
+               : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {
@@ -201,8 +211,8 @@ wide_kernel(const StepArgs a) {
     for (int s = 0; s < kStageBlocks; ++s) {
       if (KPT * 2 == kWaves && (w >> 1) != s) continue;  // D = 64
       const size_t off = (size_t)(unsigned)__builtin_amdgcn_readlane(ids, j % kWaveSize + s) * block_bytes;
-      load_to_lds(kpool + off, k_load, dst + s * (S::kBlockPieces * 16));
-      load_to_lds(vpool + off, v_load, dst + s * (S::kBlockPieces * 16) + kTileBytes);
+      const unsigned at = dst + s * (S::kBlockPieces * 16);
+      load_to_lds(kpool + off, k_load, at, vpool + off, v_load, at + kTileBytes);
     }
   };
 

@@ -43,23 +43,47 @@ namespace {
 // is one partition and no merge pass).
 //
 // A step with few (sequence, KV head) pairs instead takes the partitions that
-// make its items about one per slot of the GPU (slots_at_once), when that
-// fills at least kFillNum / kFillDen of the slots: a compute unit reads at
-// most about 64 KB at a time whatever its workgroups ask for (67 GB/s from
-// HBM), so a second item on some of them doubles the step's time, and the
-// work-order launch that few items do without is a large part of it.  GPU
-// time on MI355X, 32 / 8 heads, contexts uniform (log-uniform) up to the
-// maximum, this rule against the share: 4 sequences of up to 4096 tokens
-// 12.3 / 14.5 us (11.7 / 13.1), 8 of 4096 18.5 / 22.9 (16.8 / 17.7), 4 of 4096
-// with 64 new tokens 42.4 / 53.9 (38.6 / 37.6), 16 of 1024 with 64 new tokens
-// 38.8 / 69.2 (36.3 / 46.8).  Not where the slots stay less full (96 pairs in
-// 192 of 256 slots, contexts of 8192: 50.8 / 46.1 us), nor in partitions above
-// kFillMaxTokens: few long items wait for the longest one when the contexts
-// are log-uniform (8 of 16384 in partitions of 4096: 54.4 / 58.2, but 47.4 /
-// 34.0 us).  Contexts that are not worth a merge pass (about 3 us) stay whole:
-// up to kWholeTokens (4 sequences of 512: 7.5 / 9.0 us), and where there is no
-// second item per slot to be had up to kOneItemTokens (32 of 1024: 16.8 / 22.4
-// us; 64: 31.0 / 35.3; 64 of 2048: 56.8 / 58.2, but log-uniform 39.8 / 35.2).
+// make its items about one per slot of the GPU (slots_at_once; pieces of the
+// longest context per pair), when that fills at least kFillNum / kFillDen of the
+// slots: a compute unit reads at most about 64 KB at a time whatever its
+// workgroups ask for (67 GB/s from HBM), so a second item on some of them
+// doubles the step's time, and the work-order launch that few items do without
+// is a large part of it.  GPU time on MI355X in us, one new token, 32 / 8 heads,
+// contexts uniform up to the maximum (log-uniform in brackets), this rule
+// against the share:
+//  * where the line of 17/20 lies: 10 sequences (240 of 256 slots) of 2048 14.8 /
+//    16.1 (13.8 / 12.2), of 3072 18.1 / 21.1 (16.5 / 16.2); 14 (224 slots) of 2048
+//    18.2 / 21.0 (16.7 / 16.1); below it 13 (208) of 2048 18.2 / 19.6 (16.4 / 15.6),
+//    9 (216) 14.6 / 13.7 (13.6 / 10.4), 12 (192) 17.9 / 16.1 (16.1 / 12.5);
+//  * kFillMaxTokens: 14 of 3072 in partitions of 1536 23.7 / 26.4 (21.1 / 19.0), 10
+//    of 4096 in 1280 21.0 / 23.9 (19.1 / 18.4), 12 of 4096 in 2048 28.2 / 28.4 (25.7 /
+//    19.3): few long items wait for the longest one;
+//  * contexts not worth a merge pass stay whole, up to kWholeTokens: 4 sequences
+//    whole / in partitions of 256: of 512 8.4 / 8.7 (8.4 / 8.6), of 640 9.3 / 8.7 (9.5
+//    / 8.7), 8 of 512 8.4 / 8.9, of 640 9.6 / 9.1; and up to kWholeMoreTokens where
+//    partitions of 256 are more items than slots: 12 of 640 9.8 / 9.7 (9.4 / 8.9; all
+//    full 10.5 / 11.9), 16 of 640 10.1 / 11.0, of 768 11.5 / 12.3 (10.8 / 11.4), of 896
+//    12.8 / 12.7 (11.9 / 11.8; in 512s 12.2, 11.5);
+//  * where there is no second item per slot to be had, up to kOneItemTokens: 32 of
+//    1024 16.6 / 21.1 (14.4 / 16.2), 64 30.5 / 31.4 (22.6 / 22.2), of 1536 22.8 / 26.8 (19.0
+//    / 19.2) and 43.0 / 41.0 (31.1 / 25.6); 24 of 1024 15.3 / 16.1 (13.7 / 12.6), 48 of
+//    1536 38.0 / 33.8 (30.3 / 23.0).
+// Wide items (more than 4 query chunks) have long starts and ends and a state per
+// row to write and merge, so the more of them there are (the fewer pieces), the
+// longer their partitions (kWideFloor) and the longer the contexts that stay
+// whole (kWideWhole).  64 new tokens, whole / in partitions of 256 or 512:
+//    1 piece:  28 sequences of 1024 52.1 / 80.1 (45.9 / 68.7), of 2048 84.1 / 101.4
+//              (72.5 / 73.9), of 4096 148.2 / 150.7 (126.9 / 97.9)
+//    2:        14 of 1024 41.6 / 49.6 (40.3 / 43.4), of 1536 54.2 / 56.7 (52.7 / 46.7);
+//              of 2048 in 1024s / 512s 66.3 / 69.8 (55.4 / 49.8)
+//    3:        10 of 1024 39.2 / 44.3 (38.8 / 37.6), of 1536 52.3 / 47.9 (51.8 / 42.1)
+//    4 and 5:  8 of 576 26.9 / 30.1, of 768 31.6 / 34.3, of 1024 38.3 / 35.4; 6 of 768
+//              31.5 / 30.7, of 1024 37.8 / 33.1
+//    more:     4 of 384 21.6 / 24.2, of 448 23.1 / 24.3, of 576 26.4 / 25.6; 1 of 384
+//              20.6 / 21.0, of 448 22.3 / 21.1
+//    floors:   8 (4 pieces) of 1024 in 512s / 256s 35.4 / 36.0, of 2048 46.3 / 59.0; 4
+//              (8 pieces) of 1024 31.0 / 26.7
+// With 32 new tokens (512 slots) the same pieces give the same order.
 // Longest context a descriptor may announce: keeps every token sum of the
 // kernels (a position plus a partition size) far inside int32.
 constexpr int32_t kMaxContextTokens = 1 << 28;
@@ -70,11 +94,13 @@ constexpr int kMinPartitionTokens = 256;
 constexpr int kPartitionQuantum = 256;
 constexpr int64_t kConcurrentItems = 768;  // 256 compute units x 3 workgroups of 4 wavefronts
 constexpr int64_t kFillNum = 17, kFillDen = 20;
-constexpr int kWholeTokens = 640;          // one-tile contexts left whole
+constexpr int kWholeTokens = 512;          // one-tile contexts left whole
+constexpr int kWholeMoreTokens = 768;      // ... where splitting them makes more items than slots
 constexpr int kOneItemTokens = 1024;       // ... and when there is one for each slot
 constexpr int kFillMaxTokens = 1024;
-constexpr int kWideManyMinTokens = 1024;   // shortest partition of many wide items (their states cost more)
-constexpr int64_t kWideManyUnits = 64;
+// by pieces per pair, 6 for more: wide contexts left whole, and the shortest wide partition
+constexpr int kWideWhole[] = {2048, 1536, 1152, 768, 768, 384};
+constexpr int kWideFloor[] = {1024, 1024, 512, 512, 512, 256};
 constexpr int64_t kPrefixItemRows = 64;    // query rows of one prefix item: 4 tiles of 16
 
 int query_tokens(const pda_problem* p) { return p->num_query_tokens > 0 ? p->num_query_tokens : 1; }
@@ -147,13 +173,18 @@ int64_t filling_partition(const pda_prefix_groups* groups, int nqc, int cpg, int
   if (groups || units == 0 || (nqc > 1 && cpg == pda::kWaves)) return 0;  // (staged items run 3 to a compute unit)
   // compute units for one-tile items; pairs of wide workgroups (or one of them) otherwise
   const int64_t slots_at_once = cpg == pda::kWideChunks ? kConcurrentItems * 2 / 3 : kConcurrentItems / 3;
-  const bool one_each = 2 * units > slots_at_once && units <= kConcurrentItems;
-  if (nqc == 1 && (len <= kWholeTokens || (one_each && len <= kOneItemTokens))) return len;
+  if (nqc == 1) {
+    const bool one_each = 2 * units > slots_at_once && units <= kConcurrentItems;
+    const bool more = units * ((len + kMinPartitionTokens - 1) / kMinPartitionTokens) > slots_at_once;
+    if (len <= kWholeTokens || (more && len <= kWholeMoreTokens) || (one_each && len <= kOneItemTokens)) return len;
+  }
   const int64_t pieces = slots_at_once / units;
   if (pieces == 0 || units * pieces * kFillDen < slots_at_once * kFillNum || (nqc == 1 && pieces == 1)) return 0;
+  const int row = (int)std::min<int64_t>(pieces, 6) - 1;
+  if (nqc > 1 && len <= kWideWhole[row]) return len;
   // (to the nearest quantum: contexts are ragged, so a few items more than slots are mostly empty ones)
   int64_t tokens = std::max<int64_t>(1, (len / pieces + kPartitionQuantum / 2) / kPartitionQuantum) * kPartitionQuantum;
-  if (nqc > 1 && units >= kWideManyUnits) tokens = std::max<int64_t>(tokens, kWideManyMinTokens);
+  if (nqc > 1) tokens = std::max<int64_t>(tokens, kWideFloor[row]);
   return tokens <= kFillMaxTokens ? tokens : 0;
 }
 

@@ -2,10 +2,9 @@
 // computed (largest first, placed for the XCDs), or in natural order when
 // every item runs at once.  Two kinds of items share the launch:
 //
-// Regular items: (partition of a context, sequence, KV head, group of up to
-// 4 chunks of new query tokens; with shared-prefix groups up to 8).  A chunk
-// holds up to 16 / G consecutive new
-// tokens of the sequence, so its query rows (token-major, then the G heads of
+// Regular items: (partition of a context, sequence, KV head), with the
+// sequence's chunks of new query tokens: up to 4, with shared-prefix groups up
+// to 7.  A chunk holds up to 16 / G consecutive new tokens of the sequence, so its query rows (token-major, then the G heads of
 // the KV head) fill one 16-row MFMA tile; a decode step has one token, i.e.
 // one chunk of G rows.  New token i of a sequence with n new tokens and
 // context length L sits at position L - n + i and sees tokens
@@ -478,18 +477,14 @@ __device__ __forceinline__ bool store_other_rows(const StepArgs& a, const NewRow
 }
 
 template <int D, int MODE, int SETS>
-__device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, int b, int p) {
+__device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int g, int b, int p) {
   PassShared<D>& sh = lds.sh;
   using WA = WaveAttention<D>;
   const int Hq = a.num_q_heads;
   const int G = a.group;
-  // gc = g * NCG + chunk group (up to 4 chunks, and 8 with groups: one chunk group)
-  const int g = MODE == kModeRegister ? gc : gc / a.num_chunk_groups;
-  const int cg = MODE == kModeRegister ? 0 : gc % a.num_chunk_groups;
   const int nq = a.num_query_tokens;
-  const int CPG = a.chunks_per_group;
   // query chunks (16-row tiles) of the item: always one in the register-only variant
-  const int nchunk = MODE == kModeRegister ? 1 : min(CPG, a.num_query_chunks - cg * CPG);
+  const int nchunk = MODE == kModeRegister ? 1 : a.num_query_chunks;
   // more than 4 (wide variant only): wavefront w folds chunks w and, when it
   // exists, w + 4, and the epilogue takes the two sets of tiles in turn
   const bool two = MODE == kModeWide && nchunk > kWaves;
@@ -512,17 +507,15 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, i
   const int t0_all = seq_prefix_len(a, b);  // tokens before it belong to the group's prefix items
   // Per chunk c: its tokens [i0, i0 + nv), the token limit of its last row
   // (l_vis) and the partitions of its own tokens after the prefix.
-  auto chunk_of = [&](int t) { return cg * CPG + t; };
   auto parts_of = [&](int c) {
     const int lv = chunk_visible(a, L, c);
     const int t0 = min(t0_all, max(lv, 0));
     return lv > 0 ? (lv - t0 + Tp - 1) / Tp : 0;
   };
   int nparts_max = 0;
-  for (int t = 0; t < nchunk; ++t) nparts_max = max(nparts_max, parts_of(chunk_of(t)));
+  for (int c = 0; c < nchunk; ++c) nparts_max = max(nparts_max, parts_of(c));
   if (p == 0) {  // chunks that see nothing (L == 0, or new tokens before the context): zero rows
-    for (int t = 0; t < nchunk; ++t) {
-      const int c = chunk_of(t);
+    for (int c = 0; c < nchunk; ++c) {
       if (chunk_visible(a, L, c) > 0) continue;
       const int i0 = c * a.query_chunk;
       const int rows = min(a.query_chunk, nq - i0) * G;
@@ -543,7 +536,7 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, i
   // shared prefix, every chunk with tokens after it starts its own range at
   // the prefix's end, as the last chunk does; a chunk whose rows see nothing
   // past the prefix has no own partitions and folds nothing.
-  const int j_begin = (min(t0_all, max(chunk_visible(a, L, chunk_of(nchunk - 1)), 0)) + p * Tp) / kBlockTokens;
+  const int j_begin = (min(t0_all, max(chunk_visible(a, L, nchunk - 1), 0)) + p * Tp) / kBlockTokens;
   auto block_end = [&](int lv, int parts) {  // end block of this partition for a chunk limit lv
     const int t0 = min(t0_all, max(lv, 0));
     return p < parts ? (min(lv, t0 + (p + 1) * Tp) + kBlockTokens - 1) / kBlockTokens : 0;
@@ -625,7 +618,7 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, i
       for (int x = 0; x < kWaves; ++x) any_bad |= sh.bad[x];
     }
     for (int t = 0; t < nt; ++t) {
-      const int ct = chunk_of(t_first + t);
+      const int ct = t_first + t;
       const int ct_parts = parts_of(ct);
       if (p >= ct_parts) continue;  // the chunk sees nothing in this partition
       const int ci0 = ct * a.query_chunk;
@@ -647,7 +640,7 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, i
   };
 
   WA wave(a.scale_log2);
-  const ChunkRows ca = setup(wave, chunk_of(tile));
+  const ChunkRows ca = setup(wave, tile);
   if (MODE == kModeRegister && ntile != 1) return;  // not this launch's kind (never: the host picks the mode)
   int any_bad = 0;
   if (ntile == 1) {  // one tile: the 4 wavefronts split the blocks, tiles into registers
@@ -681,15 +674,12 @@ __device__ void regular_item(const StepArgs& a, PassLds<D, MODE>& lds, int gc, i
              });
   } else if constexpr (MODE != kModeRegister) {  // several tiles: every block staged once through LDS for all of them
     int J1 = j_begin;
-    for (int t = 0; t < nchunk; ++t) {
-      const int ct = chunk_of(t);
-      J1 = max(J1, block_end(chunk_visible(a, L, ct), parts_of(ct)));
-    }
+    for (int c = 0; c < nchunk; ++c) J1 = max(J1, block_end(chunk_visible(a, L, c), parts_of(c)));
     if constexpr (MODE == kModeWide) {
       if (two) {
         const bool has_b = tile + kWaves < nchunk;
         WA wave_b(a.scale_log2);
-        const ChunkRows cb = setup(wave_b, chunk_of(has_b ? tile + kWaves : tile));
+        const ChunkRows cb = setup(wave_b, has_b ? tile + kWaves : tile);
         run_staged<D, kStepBlocks, 2>(wave, wave_b, lds.st, table_row, j_begin, J1, block_end(ca.l_vis, ca.nparts),
                                       has_b ? block_end(cb.l_vis, cb.nparts) : 0, true, 0, 1, L, ca.l_first,
                                       max(ca.l_vis, 0), cb.l_first, max(cb.l_vis, 0), kpool, vpool, block_bytes,
@@ -817,9 +807,9 @@ partition_kernel(const StepArgs a) {
   const int item = a.order[blockIdx.x];
   // an order reused from an earlier call is the caller's contract; never step outside the items
   if ((unsigned)item >= (unsigned)(a.num_regular_items + a.num_prefix_items)) return;
-  if (item < a.num_regular_items) {  // item = (p * B + b) * HC + gc
-    const int HC = a.num_kv_heads * a.num_chunk_groups;
-    regular_item<D, MODE, SETS>(a, lds, item % HC, (item / HC) % a.num_seqs, item / (HC * a.num_seqs));
+  if (item < a.num_regular_items) {  // item = (p * B + b) * Hkv + g
+    const int H = a.num_kv_heads;
+    regular_item<D, MODE, SETS>(a, lds, item % H, (item / H) % a.num_seqs, item / (H * a.num_seqs));
   } else if constexpr (SETS == 0) {
     prefix_item<D, MODE>(a, lds, item - a.num_regular_items);
   }
@@ -828,13 +818,13 @@ partition_kernel(const StepArgs a) {
 template <int D>
 hipError_t launch_d(const StepArgs& a, hipStream_t stream) {
   const dim3 grid = a.order ? dim3((unsigned)a.num_regular_items + (unsigned)a.num_prefix_items)
-                            : dim3(a.num_kv_heads * a.num_chunk_groups, a.num_seqs, a.num_partitions);
-  // which kinds of items the step has: a regular item has one tile when its
-  // chunk group holds one query chunk; a prefix item may have one tile
+                            : dim3(a.num_kv_heads, a.num_seqs, a.num_partitions);
+  // which kinds of items the step has: a regular item has one tile when the
+  // step has one query chunk; a prefix item may have one tile
   // whenever groups exist (a row group can be small) and several when the
   // bound on a row group's rows exceeds one tile
   const bool groups = a.num_groups > 0;
-  const bool one = a.num_query_chunks % kWaves == 1 || groups;
+  const bool one = a.num_query_chunks == 1 || groups;
   const bool several =
       a.num_query_chunks >= 2 ||
       (groups && (int64_t)min(a.max_group_size, a.members_per_row_group) * a.num_query_tokens * a.group > kRows);

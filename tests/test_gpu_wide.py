@@ -11,7 +11,7 @@ import torch
 import oracle
 import workloads as W
 from parity_common import THREADS, check
-from paper_2405_11143_amd import pda_decode
+from paper_2405_11143_amd import make_problem, pda_decode, pda_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -145,3 +145,69 @@ def test_large_scores(dev, D, exponent, partition_tokens):
                 assert (np.abs(got[b, i, h] - V[best]) <= 2.0 ** -15 * np.abs(V[best])).all(), (b, i, h)
     print(f"large scores 2^{exponent}: {checked} of {total} rows", flush=True)
     assert checked > total // 2
+
+
+WIDE_SHAPES = [(8, 2, 24), (8, 2, 64), (8, 2, 100), (16, 1, 9)]  # 6, 16, 25 and 9 chunks per sequence
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,n", WIDE_SHAPES, ids=str)
+@pytest.mark.parametrize("partition_tokens", [0, 64])
+def test_out_of_range_block_ids_give_nan_rows(dev, D, Hq, Hkv, n, partition_tokens):
+    """A block id outside the pool is never dereferenced, and every row of an
+    item (up to 16 chunks of a sequence in one partition) that looks at it is
+    NaN, whichever workgroup of the item holds the row: ids that all chunks
+    see, that only the last chunk sees, and that only the second eight chunks
+    reach.  Rows of other items and sequences meet the bar."""
+    lens = [n + 200, 333, n + 37, 700, 150]
+    st = W.custom_structure(len(lens), Hq, Hkv, D, lens, seed=960 + n)
+    _, k, v = W.fill_values(st, dev, fill="nan")
+    q = W.fill_multi_q(st, n, dev)
+    qc = min(n, 16 // (Hq // Hkv))
+    nqc = -(-n // qc)
+    per_item = 16 if nqc > 8 else 8
+    tp = pda_plan(make_problem(st.B, Hq, Hkv, D, st.num_blocks, st.max_blocks_per_seq, st.max_context_len,
+                               partition_tokens, num_query_tokens=n))["partition_tokens"]
+    table = st.block_table.copy()
+    visible = lambda L, c: L - n + min(n, (c + 1) * qc)  # tokens the chunk's last row sees
+    bad = {0: [3], 1: [(333 - 1) // 16], 2: [(visible(n + 37, min(8, nqc - 1)) - 1) // 16, 1]}
+    bad[1].append((visible(333, min(per_item, nqc) - 1) - 1) // 16)  # the last block the first item looks at
+    for b, js in bad.items():
+        for i, j in enumerate(js):
+            table[b, j] = (st.num_blocks + 7, -1, 2 ** 31 - 1, -2 ** 31)[(b + i) % 4]
+    bt, ln = torch.from_numpy(table).to(dev), torch.from_numpy(st.context_lens).to(dev)
+    got = pda_decode(q, k, v, bt, ln, st.scale, max_context_len=st.max_context_len,
+                     partition_tokens=partition_tokens).cpu().numpy()
+    ref = oracle.decode_multi(W.bf16_bits(q), W.bf16_bits(k), W.bf16_bits(v), st.block_table, st.context_lens,
+                              st.scale, threads=THREADS)
+    for b, js in bad.items():
+        L = lens[b]
+        for c in range(nqc):
+            last = min(nqc, (c // per_item + 1) * per_item) - 1
+            blocks = -(-visible(L, last) // 16)  # the item's chunks look at blocks below it
+            nan = any(j < blocks and j * 16 // tp < -(-visible(L, c) // tp) for j in js)
+            rows = slice(c * qc, (c + 1) * qc)
+            assert np.isnan(got[b, rows]).all() == nan and np.isnan(got[b, rows]).any() == nan, (b, c)
+            if nan:
+                got[b, rows] = ref[b, rows]
+    check(got, ref, f"wide, bad ids n={n} D={D} Tp={partition_tokens}")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,n", WIDE_SHAPES, ids=str)
+@pytest.mark.parametrize("factor", [-1.0, 0.0, 3.0, 25.0, 1e-39])
+@pytest.mark.parametrize("partition_tokens", [0, 48])
+def test_scale_sign_zero_and_peaked(dev, D, Hq, Hkv, n, factor, partition_tokens):
+    """Negative, zero, large and subnormal scales: the kernel folds the sign
+    into q and takes a zero scale's scores from a zeroed q."""
+    lens = [1, n - 1, n + 5, 300, 1040]
+    st = W.custom_structure(len(lens), Hq, Hkv, D, lens, seed=970 + n)
+    _, k, v = W.fill_values(st, dev, fill="nan")
+    q = W.fill_multi_q(st, n, dev)
+    scale = float(np.float32(st.scale * factor))
+    bt, ln = torch.from_numpy(st.block_table).to(dev), torch.from_numpy(st.context_lens).to(dev)
+    got = pda_decode(q, k, v, bt, ln, scale, max_context_len=st.max_context_len,
+                     partition_tokens=partition_tokens).cpu().numpy()
+    ref = oracle.decode_multi(W.bf16_bits(q), W.bf16_bits(k), W.bf16_bits(v), st.block_table, st.context_lens, scale,
+                              threads=THREADS)
+    check(got, ref, f"wide, scale x{factor} n={n} D={D} Tp={partition_tokens}")

@@ -1,17 +1,18 @@
 """A CPU model of the kernels' index arithmetic (no GPU): for seeded random
-and extreme descriptors, every global address the work-order, partition and
-merge kernels form stays inside its buffer, and the work order is a
+and extreme descriptors, every global address the work-order, partition, wide
+and merge kernels form stays inside its buffer, and the work order is a
 permutation of the step's work items.
 
 The model restates, formula by formula, what pda_order.hip,
-pda_partition.hip and pda_merge.hip compute from a work item's index (its
-partition, sequence, KV head and chunk group, or its shared-prefix group),
-with the partition size, partition count and workspace taken from the
-library's own plan (pda_plan / pda_plan_shared_prefix).  Tile loads are
-bounds-checked by their buffer descriptors on the GPU; what is modelled here
-is everything else: block-table entries read, query rows read, output rows
-and partial states written, the workspace carving, and the LDS indices of the
-staged path.
+pda_partition.hip, pda_wide.hip and pda_merge.hip compute from a work item's
+index (its partition, sequence, KV head and chunk group, or its shared-prefix
+group), with the partition size, partition count and workspace taken from the
+library's own plan (pda_plan / pda_plan_shared_prefix).  The partition kernel's
+tile loads are bounds-checked by their buffer descriptors on the GPU; the wide
+kernel's go straight to LDS, so their offsets in the tile and in LDS are
+modelled, as is everything else: block-table entries read, query rows read,
+output rows and partial states written, the workspace carving, and the LDS
+indices of the staged paths.
 """
 import numpy as np
 import pytest
@@ -23,6 +24,8 @@ WAVES, WAVE = 4, 64
 MAX_GROUP = 16
 ORDER_BUCKETS = 256
 ID_WINDOW = 256
+WG_CHUNKS = 2 * WAVES  # chunks of a workgroup of the wide kernel
+WIDE_BUFFERS, WIDE_WINDOW = 4, 1024
 
 
 def plan_of(B, Hq, Hkv, D, mbps, mcl, tp, n, groups=None):
@@ -111,22 +114,18 @@ def model_order(B, Hkv, lens_c, mcl, pl, seq_prefix=None, groups=None):
 
 def check_regular_item(item, B, Hq, Hkv, D, n, mbps, mcl, lens_c, pl, seq_prefix, touched):
     G, qc, nqc, cpg, ncg, Tp = pl["G"], pl["qc"], pl["nqc"], pl["cpg"], pl["ncg"], pl["Tp"]
-    HC = Hkv * ncg
-    gc = item % HC
-    b = (item // HC) % B
-    p = item // (HC * B)
-    g, cg = gc // ncg, gc % ncg
-    assert 0 <= b < B and 0 <= g < Hkv and 0 <= p < pl["P"] and 0 <= cg < ncg
-    nw = 2 * WAVES if cpg > 2 * WAVES else WAVES  # wavefronts of the launch's workgroups
-    nchunk = min(cpg, nqc - cg * cpg)  # the register-only variant runs only when every item has one chunk
-    assert 1 <= nchunk <= (2 * nw if cpg > WAVES else nw)
-    two = cpg > WAVES and nchunk > nw
-    ntile = nw if two else nchunk
-    slices = nw // ntile
-    # the LDS epilogue arrays have nw entries: row_weights reads entry t + x * ntile (t < ntile, x < slices)
-    assert slices >= 1 and ntile * slices <= nw
-    if two:
-        assert nchunk <= 2 * nw  # wavefront w folds chunks w and w + nw
+    assert ncg == 1  # (several chunk groups: the wide kernel)
+    b = (item // Hkv) % B
+    p = item // (Hkv * B)
+    g = item % Hkv
+    assert 0 <= b < B and 0 <= g < Hkv and 0 <= p < pl["P"]
+    nchunk = nqc  # the register-only variant runs only when every item has one chunk
+    assert 1 <= nchunk <= (2 * WAVES if cpg > WAVES else WAVES)
+    two = cpg > WAVES and nchunk > WAVES  # wavefront w folds chunks w and w + 4
+    ntile = WAVES if two else nchunk
+    slices = WAVES // ntile
+    # the LDS epilogue arrays have 4 entries: row_weights reads entry t + x * ntile (t < ntile, x < slices)
+    assert slices >= 1 and ntile * slices <= WAVES
     L = min(max(lens_c[b], 0), mcl)
     t0_all = seq_prefix[b] if seq_prefix is not None else 0
     rows_q = B * n * Hq
@@ -136,8 +135,7 @@ def check_regular_item(item, B, Hq, Hkv, D, n, mbps, mcl, lens_c, pl, seq_prefix
         t0 = min(t0_all, max(lv, 0))
         return -(-(lv - t0) // Tp) if lv > 0 else 0
 
-    chunks = [cg * cpg + t for t in range(nchunk)]
-    assert all(c < nqc for c in chunks)
+    chunks = list(range(nchunk))
     nparts_max = max(parts_of(c) for c in chunks)
     for c in chunks:
         i0 = c * qc
@@ -180,6 +178,131 @@ def check_regular_item(item, B, Hq, Hkv, D, n, mbps, mcl, lens_c, pl, seq_prefix
                 slot = row * pl["S"] + pl["Pp"] + p
                 assert pl["split"] and 0 <= slot < pl["slots"], (slot, pl["slots"])
                 touched["slots"].add(slot)
+
+
+def check_wide_workgroup(item, half, halves, B, Hq, Hkv, n, mbps, mcl, lens_c, pl, touched):
+    """One workgroup of the wide kernel: chunks [c_first, c_end) of its item."""
+    G, qc, nqc, cpg, ncg, Tp = pl["G"], pl["qc"], pl["nqc"], pl["cpg"], pl["ncg"], pl["Tp"]
+    HC = Hkv * ncg
+    gc, b, p = item % HC, (item // HC) % B, item // (HC * B)
+    g, cg = gc // ncg, gc % ncg
+    assert 0 <= b < B and 0 <= g < Hkv and 0 <= p < pl["P"] and 0 <= cg < ncg and halves * WG_CHUNKS == cpg
+    item_first = cg * cpg
+    item_end = min(nqc, item_first + cpg)
+    c_first = item_first + half * WG_CHUNKS
+    c_end = min(item_end, c_first + WG_CHUNKS)
+    if c_first >= c_end:
+        return
+    L = min(max(lens_c[b], 0), mcl)
+
+    def parts_of(c):
+        lv = chunk_visible(L, n, qc, c)
+        return -(-lv // Tp) if lv > 0 else 0
+
+    def row_of(c, r):
+        row = (b * n + c * qc + r // G) * Hq + g * G + r % G
+        assert 0 <= row < B * n * Hq
+        return row
+
+    rows = {c: min(qc, n - c * qc) * G for c in range(c_first, c_end)}
+    assert all(1 <= r <= MAX_GROUP for r in rows.values())
+    if p == 0:
+        for c in range(c_first, c_end):
+            if chunk_visible(L, n, qc, c) > 0:
+                break
+            touched["out"].update(row_of(c, r) for r in range(rows[c]))
+    if p >= parts_of(c_end - 1):
+        return
+    t_pe = (p + 1) * Tp
+    assert t_pe < 2 ** 31
+
+    def vis_blocks(c):
+        return -(-min(max(chunk_visible(L, n, qc, c), 0), t_pe) // BS)
+
+    J0, J1 = p * Tp // BS, vis_blocks(c_end - 1)
+    assert 0 <= J0 < J1 <= vis_blocks(item_end - 1) <= -(-L // BS) <= mbps  # (the other half's ids are looked at too)
+    for jw in range(J0, J1, WIDE_WINDOW):
+        check_wide_window(min(J1, jw + WIDE_WINDOW) - jw)
+    for w in range(WAVES):
+        ca = c_first + 2 * w
+        for c in (ca, ca + 1):
+            if c >= c_end or p >= parts_of(c):
+                continue
+            for h in range(rows[c]):  # its lane rows: column 16 (c - ca) + h of the tile
+                row = row_of(c, h)
+                if parts_of(c) == 1:
+                    touched["out"].add(row)
+                else:
+                    slot = row * pl["S"] + p
+                    assert pl["split"] and 0 <= slot < pl["slots"]
+                    touched["slots"].add(slot)
+
+
+def check_wide_window(blocks):
+    """The block ids in LDS that the loads of one window of `blocks` read."""
+    n_ids = min(WIDE_WINDOW, (blocks + WIDE_BUFFERS * 2 + WAVE) // WAVE * WAVE)
+    nsteps = -(-blocks // 2)
+    assert blocks <= WIDE_WINDOW
+    loaded = None
+    for step in range(nsteps + WIDE_BUFFERS - 1):  # the prologue's 3, then one in each step
+        j = min(step * 2, WIDE_WINDOW - 2)
+        if j % WAVE == 0:
+            loaded = j
+            assert j + WAVE <= WIDE_WINDOW  # ids[j + lane]
+        assert loaded <= j and j + 1 < loaded + WAVE  # readlane j % 64 and the one after it
+        assert j + 1 < n_ids  # both were filled
+
+
+def wide_lds_indices(D):
+    """The wide kernel's loads to LDS, its K and V reads and its epilogue."""
+    tile = BS * D * 2
+    tile_pieces, RP = 2 * D, D // 8
+    block_pieces = 2 * tile_pieces
+    KPT = tile // 1024
+    buf_bytes = WIDE_BUFFERS * 2 * block_pieces * 16
+    assert buf_bytes <= 1 << 16  # an LDS address that M0 holds in 16 bits
+    source = {}  # LDS byte of a step -> (block, side, byte of the tile)
+    for w in range(WAVES):
+        for lane in range(WAVE):
+            k_load = (w % KPT) * 1024 + lane * 16
+            v_row = lane // RP
+            perm = 4 * (v_row & 3) if D == 128 else 4 * ((v_row >> 1) & 1)
+            v_load = (w % KPT) * 1024 + v_row * (2 * D) + 16 * ((lane % RP) ^ perm)
+            for s in range(2):
+                if KPT * 2 == WAVES and w >> 1 != s:
+                    continue
+                at = (w % KPT) * 1024 + s * block_pieces * 16 + 16 * lane
+                for side, offset, dst in (("k", k_load, at), ("v", v_load, at + tile)):
+                    assert 0 <= offset <= tile - 16 and dst not in source
+                    source[dst] = (s, side, offset)
+    assert sorted(source) == list(range(0, 2 * block_pieces * 16, 16))  # every piece of a step, once
+    assert len(set(source.values())) == len(source)
+    for lane in range(WAVE):
+        hh, col = lane >> 5, lane & 31
+        for c in range(D // 16):  # K: token col, elements 16 c + 8 hh .. + 7
+            piece = (col >> 4) * block_pieces + hh * 16 + (lane & 15) + 32 * c
+            assert source[16 * piece] == (col >> 4, "k", 16 * (16 * (2 * c + hh) + (lane & 15)))
+        s16 = lane & 15
+        for m in range(2):  # V: rows 4 hh + s16 / 4 (+ 8) of block m, 4 columns from 32 t + 16 u + 4 (s16 % 4)
+            for t in range(D // 32):
+                tr = (4 * hh + s16 // 4) * D + 16 * ((lane >> 4) & 1) + 4 * (s16 & 3)
+                tr += 32 * (t ^ (s16 // 4 if D == 128 else s16 // 8))
+                for extra in (0, 8):
+                    byte = (tile_pieces + m * block_pieces) * 16 + 2 * (tr + extra * D)
+                    blk, side, src = source[byte // 16 * 16]
+                    row, column = 4 * hh + s16 // 4 + extra, 32 * t + 16 * ((lane >> 4) & 1) + 4 * (s16 & 3)
+                    assert (blk, side, src + byte % 16) == (m, "v", 2 * (row * D + column))
+        for x in range(32):  # the rows added apart: 8 columns' pieces of row x
+            perm = 4 * (x & 3) if D == 128 else 4 * ((x >> 1) & 1)
+            for tk in range(D // 8):
+                piece = (x // 16) * block_pieces + tile_pieces + (x % 16) * RP + (tk ^ perm)
+                assert source[16 * piece] == (x // 16, "v", 2 * ((x % 16) * D + 8 * tk))
+    assert WAVES * 32 * (D // 4) * 16 <= buf_bytes  # the epilogue's rows
+    for col in range(32):
+        swz = col & (D // 4 - 1)
+        units = [(8 * t + 2 * k + hh) ^ swz for t in range(D // 32) for k in range(4) for hh in range(2)]
+        assert sorted(units) == list(range(D // 4))
+        assert [u ^ swz for u in units] == list(range(D // 4))  # read back as columns 4 u
 
 
 def check_prefix_item(pitem, B, Hq, Hkv, D, n, mcl, mbps, lens_c, pl, groups, touched):
@@ -238,16 +361,16 @@ def check_merge(B, Hq, n, mcl, lens_c, pl, seq_prefix, touched):
     assert len(touched["out"]) == B * n * Hq, "every output row is written"
 
 
-def staged_lds_indices(D, nw=WAVES):
+def staged_lds_indices(D):
     """The staging buffer's piece indices and the transposed V reads stay in one block."""
     TC = 16 * D * 2 // 16
     RP = D // 8
     block_pieces = TC + BS * (RP + 2)
-    loads = 2 * 2 * TC // (nw * WAVE)
-    assert loads * nw * WAVE == 2 * 2 * TC  # every piece of a step is loaded once
-    for tid in range(nw * WAVE):
+    loads = 2 * 2 * TC // (WAVES * WAVE)
+    assert loads * WAVES * WAVE == 2 * 2 * TC  # every piece of a step is loaded once
+    for tid in range(WAVES * WAVE):
         for k in range(loads):
-            ci = k * nw * WAVE + tid
+            ci = k * WAVES * WAVE + tid
             pc = ci % TC
             blk = ci // (2 * TC)
             dst = blk * block_pieces + (TC + pc // RP * (RP + 2) + pc % RP if (ci // TC) & 1 else pc)
@@ -280,6 +403,20 @@ def run_case(rng, B, Hq, Hkv, D, n, mcl, tp, lens, mbps, groups=None):
     assert len(order) == pl["items"]
     assert pl["slots"] * (D + 2) * 4 + len(order) * 4 <= pl["ws"]  # states, then the order (then prefixes)
     touched = {"out": set(), "slots": set()}
+    if pl["cpg"] > WAVES and not groups:  # the wide kernel: workgroup -> (place in the order, half of the item)
+        halves = pl["cpg"] // WG_CHUNKS
+        grid = (pl["items"] + 7) // 8 * 16 if halves == 2 else pl["items"]
+        seen = set()
+        for bid in range(grid):
+            slot, half = ((bid >> 4) * 8 + (bid & 7), (bid >> 3) & 1) if halves == 2 else (bid, 0)
+            if slot >= pl["regular"]:
+                continue
+            assert (slot, half) not in seen
+            seen.add((slot, half))
+            check_wide_workgroup(int(order[slot]), half, halves, B, Hq, Hkv, n, mbps, mcl, lens_c, pl, touched)
+        assert len(seen) == pl["regular"] * halves
+        check_merge(B, Hq, n, mcl, lens_c, pl, seq_prefix, touched)
+        return
     for item in range(pl["items"]):
         if item < pl["regular"]:
             check_regular_item(item, B, Hq, Hkv, D, n, mbps, mcl, lens_c, pl, seq_prefix, touched)
@@ -291,7 +428,16 @@ def run_case(rng, B, Hq, Hkv, D, n, mcl, tp, lens, mbps, groups=None):
 @pytest.mark.parametrize("D", [64, 128])
 def test_staged_lds_indices(D):
     staged_lds_indices(D)
-    staged_lds_indices(D, nw=2 * WAVES)  # workgroups of 8 wavefronts (items of more than 8 chunks)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_wide_lds_indices(D):
+    wide_lds_indices(D)
+
+
+def test_wide_id_windows():
+    for blocks in range(1, WIDE_WINDOW + 1):
+        check_wide_window(blocks)
 
 
 def test_random_descriptors():

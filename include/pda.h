@@ -169,8 +169,8 @@ int pda_partition_attention(const pda_problem *prob, const void *q, const void *
                             void *workspace, size_t workspace_bytes, hipStream_t stream);
 
 /* Pass 2 alone: merge the partial states that pass 1 left in `workspace` into
- * `out` for every row that sees more than one partition, in ascending
- * partition order.  Must follow pass 1 for the same descriptor and lengths. */
+ * `out` for every row that sees more than one partition, in a fixed order.
+ * Must follow pass 1 for the same descriptor and lengths. */
 int pda_merge_partitions(const pda_problem *prob, const int32_t *context_lens, float *out,
                          const void *workspace, size_t workspace_bytes, hipStream_t stream);
 

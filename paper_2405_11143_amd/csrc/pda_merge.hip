@@ -22,12 +22,16 @@
 // With many rows (several new tokens per sequence) the merge streams tens to
 // hundreds of MB, and what counts is the wavefronts in flight and the vector
 // instructions of a row: rows of up to kFewSlots or kSpec slots have variants
-// without the loop over further slots (22 and 33 VGPRs at D = 128 against 83: 8
-// wavefronts per SIMD instead of 5), and whatever is the same for a wavefront is
-// scalar (169 and 210 vector instructions).  Whole steps, one kernel for all
-// against these: 64 new tokens over 64 long contexts (131072 rows of 2 slots)
+// without the loop over further slots (22 and 33 VGPRs at D = 128 against 73: 8
+// wavefronts per SIMD instead of 6; 83 and 5 when this was measured), and
+// whatever is the same for a wavefront is scalar (169 and 210 vector
+// instructions).  Whole steps, one kernel for all against these: 64 new tokens over 64 long contexts (131072 rows of 2 slots)
 // 616 -> 601 us, 4 over 188 (12032 rows of 6) 56.8 -> 55.8, 11 over 22 (9680 of
-// 6) 53.2 -> 52.3, 4 over 303 (19392 of 3) 44.5 -> 43.2.
+// 6) 53.2 -> 52.3, 4 over 303 (19392 of 3) 44.5 -> 43.2.  That is what such steps
+// took before outputs were loaded early (55.9, 52.3, 44.0): the early loads are
+// for small steps.  Lengths first where rows are many was measured as well: 12
+// new tokens over 77 (29568 rows of 2, most of them whole) +-0, the other two
+// 56.0 -> 56.5 and 52.6 -> 53.5, 64 over 64 610 -> 600.
 #include "pda_internal.h"
 
 namespace pda {

@@ -4,9 +4,11 @@
 // A work item is (partition of a context, sequence, KV head, group of up to 8
 // or 16 chunks), as in pda_partition.hip; a workgroup of 4 wavefronts takes 8
 // chunks of it (an item of 16 is two workgroups), and each wavefront two
-// neighbouring chunks, 32 query rows.  These steps are bound by the matrix
-// cores and, with them busy, by the chip's power: the clock falls to about
-// 1.75 GHz with the MFMA pipes 64% busy.  What follows from that:
+// neighbouring chunks, 32 query rows.  Chunked prefill is bound by the matrix
+// cores and, with them busy, by the chip's power: the clock falls to about 1.8
+// GHz with the MFMA pipes busy on 59% of the cycles, VALU instructions issued on
+// 52% and both at once on 25%.  Fresh prompts (pipes 24% busy) wait for the starts
+// and ends of many short items.  What follows from that:
 //  * Both products on MFMA f32_32x32x16_bf16, transposed as in pda_wave.h
 //    (S^T = K Q^T, O^T = V^T P^T): one instruction of 32 cycles keeps a SIMD's
 //    pipe full from a single wavefront and leaves room for 4-6 VALU
@@ -18,20 +20,21 @@
 //    24 MFMAs and the softmax of a step are one stretch without a branch
 //    (1561 -> 1501 us on the step below).
 //  * K and V tiles go straight from memory to LDS (16 bytes per lane), a
-//    32-token step at a time, one folded and three in flight.  Through
-//    registers (two buffers of 64 tokens) the same fold took 1731 us: the
-//    LDS writes and the registers' loads waited on each other.
+//    32-token step at a time in four buffers: one step is folded, the next
+//    one's scores are formed, two are in flight.  Through registers (two
+//    buffers of 64 tokens) the same fold took 1731 us: the LDS writes and the
+//    registers' loads waited on each other.
 //  * Cached loads: each tile is read by every workgroup that shares the
-//    (sequence, KV head), and 88% of them hit the XCD's L2 (non-temporal
-//    loads: 48%, 1734 us).
+//    (sequence, KV head), and 89% of the requests hit the XCD's L2
+//    (non-temporal loads: 48%, 1734 us).
 //  * Two independent workgroups of 4 wavefronts per compute unit; one of 8,
 //    which halves the tile loads but keeps its wavefronts in step, took
 //    1585 us.
 // 32 sequences of 1024-8192 tokens, 512 of them new, 32 / 8 heads, D = 128:
-// 1831 -> 1510 us against 8 wavefronts of two 16-row tiles each (775 TFLOP/s
-// of attention, 1160 issued with P in two halves); 64 new tokens over 64
+// 1831 -> 1520 us against 8 wavefronts of two 16-row tiles each (768 TFLOP/s
+// of attention, 1152 issued with P in two halves); 64 new tokens over 64
 // contexts of up to 16384: 690 -> 600 us; 48 prompts of up to 1024 tokens
-// (28 / 4 heads): 755 -> 432 us.
+// (28 / 4 heads), the append of their K and V among it: 754 -> 428 us.
 #include "pda_wave.h"
 
 namespace pda {
@@ -42,7 +45,7 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kTileRows = 32;          // query rows of a wavefront: two 16-row chunks
 constexpr int kWgChunks = 2 * kWaves;  // chunks of a workgroup
 constexpr int kStageBlocks = 2;        // blocks of a staged step: 32 tokens
-constexpr int kBuffers = 4;            // one step folded, three in flight
+constexpr int kBuffers = 4;            // one step folded, the next one's scores formed, two in flight
 constexpr int kWindow = 1024;          // block ids held in LDS at a time
 constexpr float kExactMax = 128.f;     // running maxima whose rounding is below P's resolution
 

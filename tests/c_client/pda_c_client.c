@@ -13,7 +13,7 @@
  * entry point without
  * allocation (pda_decode_noalloc) give bitwise the same output, and that
  * invalid arguments come back as status codes.  Then 40 new tokens per
- * sequence on the same cache (workgroups of 8 wavefronts, two 16-row tiles
+ * sequence on the same cache (items of 10 query chunks, two workgroups
  * each) against the oracle's multi-token attention, and token
  * log-probabilities and entropies of seeded bf16 logits (a small batch,
  * rows split over workgroups through the workspace) against the oracle's.

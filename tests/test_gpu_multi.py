@@ -53,11 +53,11 @@ CASES = [  # (Hq, Hkv, D, n): rows per work item = min(n, 16 // G) * G
     (32, 8, 128, 13),  # G=4: 4 chunks (3 full, 1 partial) in one item
     (32, 8, 64, 21),   # G=4: 6 chunks in one item, two tiles on wavefronts 0-1
     (4, 4, 128, 40),   # G=1: 3 chunks (16 + 16 + 8 tokens)
-    (32, 8, 128, 32),  # G=4: 8 chunks in one item, two tiles per wavefront
-    (8, 1, 128, 12),   # G=8: 6 chunks, two tiles on wavefronts 0-1
+    (32, 8, 128, 32),  # G=4: 8 chunks in one item, two on each wavefront's tile
+    (8, 1, 128, 12),   # G=8: 6 chunks on three wavefronts
     (12, 4, 128, 26),  # G=3: 6 chunks of 5 tokens (the last one 1), 15 rows each
-    (32, 8, 128, 37),  # G=4: 10 chunks in one item on 8 wavefronts (two tiles on wavefronts 0-1)
-    (32, 8, 128, 64),  # G=4: 16 chunks in one item, two tiles on each of 8 wavefronts
+    (32, 8, 128, 37),  # G=4: 10 chunks in one item of two workgroups (8 + 2)
+    (32, 8, 128, 64),  # G=4: 16 chunks in one item of two full workgroups
     (32, 8, 128, 72),  # G=4: 18 chunks, two items (16 + 2 chunks)
     (8, 1, 128, 40),   # G=8: 20 chunks of 2 tokens, two items (16 + 4 chunks)
 ]
@@ -65,8 +65,8 @@ CASES = [  # (Hq, Hkv, D, n): rows per work item = min(n, 16 // G) * G
 
 def test_many_chunk_groups(dev):
     """128 new tokens at G = 4: 32 query chunks in 2 work items of 16 chunks
-    (8 wavefronts of two tiles) per (partition, sequence, KV head), every
-    element against the oracle."""
+    (two workgroups each) per (partition, sequence, KV head), every element
+    against the oracle."""
     lens = [1, 200, 700, 3000, 128, 1500]
     n = 128
     st = W.custom_structure(len(lens), 32, 8, 128, lens, seed=73)
@@ -173,13 +173,15 @@ def test_multi_token_poison_and_shuffle_bit_identical(dev, n):
 @pytest.mark.parametrize("n", [1, 8, 32, 60], ids=["register", "mixed", "wide", "wide16"])
 @pytest.mark.parametrize("partition_tokens", [0, 64])
 def test_run_to_run_bitwise_every_variant(dev, D, n, partition_tokens):
-    """Three runs give identical bits in each compiled variant of the
-    partition kernel at both head dims: one 16-row tile per item in registers
-    (n = 1), up to 4 tiles staged through LDS (n = 8 at G = 4: 2 tiles), the
-    wide variant with two tiles per wavefront (n = 32: 8 tiles) and its
-    8-wavefront form (n = 60: 15 tiles); with whole and split contexts.  These runs guard the ordering of the score
-    MFMAs and their first VALU reads, which the compiler once left without
-    the wait states a read of an MFMA result needs."""
+    """Three runs give identical bits in the partition kernel's variants for
+    steps without groups, at both head dims -- one 16-row tile per item in
+    registers (n = 1), up to 4 tiles staged through LDS (n = 8 at G = 4: 2
+    tiles) -- and in the wide kernel, with one workgroup per item (n = 32: 8
+    chunks) and with two (n = 60: 15 chunks); with whole and split contexts.
+    (The variant of two tiles per wavefront, which only steps with
+    shared-prefix groups reach, is repeated in their tests.)  These runs guard
+    the ordering of the score MFMAs and their first VALU reads, which the
+    compiler once left without the wait states a read of an MFMA result needs."""
     lens = [1, 17, 300, 2049, 40, 64, 1000, 513]
     st = W.custom_structure(len(lens), 32, 8, D, lens, seed=300 + n + D)
     _, k, v = W.fill_values(st, dev, fill="nan")

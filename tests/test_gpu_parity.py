@@ -289,7 +289,7 @@ def test_nan_inside_a_context_propagates_like_the_oracle(dev, n, partition_token
     rows; everything else is unaffected.  The positions of NaN outputs equal
     the oracle's and the other elements meet the bar.  The poisoned tokens
     come before the new tokens, so every row of the sequence sees them (the
-    register path, the staged path and 8-wavefront items; whole and split
+    register path, the staged path and the wide kernel; whole and split
     contexts)."""
     lens = [200, 300, 150, 1000, 777]
     st = W.custom_structure(len(lens), 32, 8, 128, lens, seed=95 + n)

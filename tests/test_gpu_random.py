@@ -2,7 +2,7 @@
 every output element: group sizes G = 1 ... 16 (odd ones included), head
 dims 64 and 128, 1 to 70 new tokens per sequence (every kernel variant:
 one tile in registers, up to 4 tiles staged, wide items of 5-8 chunks and
-of 9-16 chunks on 8 wavefronts, several chunk groups), ragged contexts with
+of 9-16 chunks in two workgroups, several chunk groups), ragged contexts with
 empty ones and ones shorter than the new tokens, automatic and forced
 partition sizes (split contexts and the merge).  Same bar as the other
 parity tests.  PDA_RANDOM_CASES sets the number of seeds (32 by default; a

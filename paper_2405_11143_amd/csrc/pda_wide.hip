@@ -31,10 +31,10 @@
 //    which halves the tile loads but keeps its wavefronts in step, took
 //    1585 us.
 // 32 sequences of 1024-8192 tokens, 512 of them new, 32 / 8 heads, D = 128:
-// 1831 -> 1520 us against 8 wavefronts of two 16-row tiles each (768 TFLOP/s
-// of attention, 1152 issued with P in two halves); 64 new tokens over 64
-// contexts of up to 16384: 690 -> 600 us; 48 prompts of up to 1024 tokens
-// (28 / 4 heads), the append of their K and V among it: 754 -> 428 us.
+// 1853 -> 1586 us against 8 wavefronts of two 16-row tiles each (738 TFLOP/s
+// of attention, 1107 issued with P in two halves); 64 new tokens over 64
+// contexts of up to 16384: 706 -> 622 us; 48 prompts of up to 1024 tokens
+// (28 / 4 heads), the append of their K and V among it: 754 -> 432 us.
 #include "pda_wave.h"
 
 namespace pda {

@@ -266,10 +266,10 @@ int pda_append_kv(const pda_problem *prob, const void *k_new, const void *v_new,
 
 /* pda_append_kv followed by pda_decode, for one new token per sequence
  * (num_query_tokens 0 or 1; the KV-cache management and attention of one
- * rollout step, Section 3.2 and Appendix C).  In steps of up to 128 sequences
+ * rollout step, Section 3.2 and Appendix C).  In steps of up to 256 sequences
  * whose pass-1 work items all run at once (a small batch, where each launch is a
- * large part of the step) or whose contexts are split into 3 partitions or more,
- * the append is folded into pass 1: a wavefront first stores the new K and V
+ * large part of the step), and of up to 128 whose contexts are split into 3
+ * partitions or more, the append is folded into pass 1: a wavefront first stores the new K and V
  * rows that go to the blocks it reads, whichever sequence they belong to, and
  * the step needs no append launch.  Other steps run the append kernel first.
  * Arguments are those of pda_append_kv and pda_decode; the caches and the output

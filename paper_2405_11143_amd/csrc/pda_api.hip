@@ -380,8 +380,8 @@ hipError_t launch_append_of(const pda_problem* p, const pda::StepArgs& args, con
 
 // Whether a step folds its KV append into pass 1: one new token per sequence,
 // at most kFoldMaxSeqs sequences (every wavefront looks through all their new
-// rows, kept in registers), and either every work item runs at once or contexts
-// are split into kFoldPartitions or more.  The launch saved is about 2 us of the
+// rows, kept in registers), and either every work item runs at once or up to
+// kFoldSplitSeqs contexts are split into kFoldPartitions or more.  The launch saved is about 2 us of the
 // step; what it costs is that the wavefronts that store a new row wait for it
 // before they stream, one in four of an item that ends a context.  Where
 // every item does and none of them can wait beside another (one partition, more
@@ -391,13 +391,16 @@ hipError_t launch_append_of(const pda_problem* p, const pda::StepArgs& args, con
 // 17.1; split contexts: 8 of 16384 (22 partitions) 51.7 / 53.8, 64 of 2048 55.3 /
 // 57.5, 48 of 4096 75.7 / 75.7, 64 of 8192 178.2 / 179.0, and planned for 8192
 // with contexts of up to 1024, where most items end one, 36.2 / 38.5; 32 of
-// 16384 181.3 / 176.9 (180.0 / 181.2 in other memory).  Two partitions: 64
+// 16384 181.3 / 176.9 (180.0 / 181.2 in other memory).  More sequences: 192 of 512
+// with 4 KV heads, all at once, 25.5 / 27.1, 256 of 512 with one 11.9 / 13.1; 256 of
+// 512 in a step planned for 16384 (8192 items) 73.8 / 72.1.  Two partitions: 64
 // sequences of 1024 with 16 KV heads 58.9 / 59.5; one: 64 of 2048 with 32
 // 184.2 / 182.7.
-constexpr int kFoldPartitions = 3;
+constexpr int kFoldPartitions = 3, kFoldSplitSeqs = 128;
 bool folds_append(const pda_problem* p, const Plan& plan) {
   return query_tokens(p) == 1 && p->num_seqs <= pda::kFoldMaxSeqs &&
-         (plan.items <= (size_t)concurrent_items(plan) || plan.info.num_partitions >= kFoldPartitions);
+         (plan.items <= (size_t)concurrent_items(plan) ||
+          (plan.info.num_partitions >= kFoldPartitions && p->num_seqs <= kFoldSplitSeqs));
 }
 
 // Let pass 1 store the step's new K/V rows (one new token per sequence, no

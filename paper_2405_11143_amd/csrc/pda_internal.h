@@ -13,7 +13,7 @@ constexpr int kWaves = 4;         // wavefronts per partition workgroup
 constexpr int kMaxGroup = 16;     // query heads per KV head: one 16-row MFMA tile
 constexpr int kWideChunks = 2 * kWaves;  // query chunks of a work item with more than 4: two per wavefront
 constexpr int kWide16Chunks = 4 * kWaves;  // with more than 8: two workgroups of kWideChunks
-constexpr int kFoldMaxSeqs = 128;  // sequences of a step that folds its KV append into pass 1
+constexpr int kFoldMaxSeqs = 256;  // sequences of a step that folds its KV append into pass 1
 constexpr int kOrderThreads = 1024;  // the work-order kernel is one workgroup of this size
 constexpr int kOrderBuckets = 256;   // size classes of its counting sort (partition blocks, capped)
 

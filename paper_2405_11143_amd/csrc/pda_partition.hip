@@ -80,8 +80,8 @@ struct Staging {
 
 // Which paths a launch compiles.  A launch whose items all have one tile
 // (every decode step without shared-prefix groups) compiles the register
-// path only (138 VGPRs at D = 128, 33 KiB of LDS; with a folded append 141, or
-// 144 for more than 64 sequences); with up to 4 query chunks
+// path only (138 VGPRs at D = 128, 33 KiB of LDS; with a folded append 141, 144
+// for more than 64 sequences and 148 for more than 128); with up to 4 query chunks
 // per item both paths are compiled (167 VGPRs, 50.5 KiB); with more, which
 // comes here only with shared-prefix groups, the wide variant also folds two
 // tiles per wavefront (241 VGPRs, 2 workgroups per compute unit).
@@ -386,10 +386,12 @@ __device__ void run_staged(WaveAttention<D>& wave, WaveAttention<D>& wave_b, Sta
 // But sequences may share blocks -- several rows of one context with lengths
 // L, L + 1, ..., each appending its own token, say -- and then a wavefront reads
 // rows that other workgroups store in this launch.  Nothing orders the two, so
-// it stores those rows itself: every writer of a slot writes the same bytes,
-// and the wavefront's later loads miss its compute unit's L1 (stores do not
-// allocate there), so they see them.  The wavefront's own row is stored first:
-// the search for the others runs while it waits for that store.
+// it stores those rows itself: every writer of a slot writes the same bytes, and
+// loads that follow a wavefront's completed stores see them (its compute unit's
+// L1 is written through and coherent with the unit's own accesses).  The
+// wavefront's own row is stored first: the search for the others runs while it
+// waits for that store, or behind the first tiles' loads, which are issued again
+// after a find.
 
 // The lane's 16-byte piece of sequence b's new row of KV head g (lanes below
 // D / 8: K, the next D / 8: V), and its place in slot `slot` of block `phys`.
@@ -833,6 +835,8 @@ hipError_t launch_d(const StepArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL((partition_kernel<D, kModeWide>), grid, block, 0, stream, a);
   else if (a.k_new && a.num_seqs <= kWaveSize)
     hipLaunchKernelGGL((partition_kernel<D, kModeRegister, 1>), grid, block, 0, stream, a);
+  else if (a.k_new && a.num_seqs <= 2 * kWaveSize)
+    hipLaunchKernelGGL((partition_kernel<D, kModeRegister, 2>), grid, block, 0, stream, a);
   else if (a.k_new)
     hipLaunchKernelGGL((partition_kernel<D, kModeRegister, kFoldMaxSeqs / kWaveSize>), grid, block, 0, stream, a);
   else if (one && !several)

@@ -193,7 +193,7 @@ def test_decode_append_matches_two_calls(dev, case):
     plan = pda_plan(make_problem(st.B, st.Hq, st.Hkv, st.D, st.num_blocks, st.max_blocks_per_seq,
                                  st.max_context_len, tp))
     items = st.B * st.Hkv * plan["num_partitions"]
-    folded = st.B <= 128 and (items <= 768 or plan["num_partitions"] >= 3)
+    folded = st.B <= 256 and (items <= 768 or (plan["num_partitions"] >= 3 and st.B <= 128))
     assert folded == (case not in ("two_partitions", "llama3_8b"))
     print(f"decode_append {case}: {items} work items ({'folded' if folded else 'append kernel first'})")
     q, k, v = W.fill_values(st, dev, fill="nan")
@@ -224,7 +224,9 @@ SHARED_CASES = {
     "split": (2, 4, 700, 32, 8, 128, 256),          # 3 partitions, every item at once
     "many": (24, 5, 333, 32, 8, 128, 112),          # 3 partitions, 120 rows, 2880 items
     "two_partitions": (24, 5, 333, 32, 8, 128, 176),  # 1920 items, 2 partitions
-    "over_128": (40, 4, 333, 32, 8, 128, 112),       # more sequences than a folded append looks through
+    "over_128": (40, 4, 333, 32, 8, 128, 112),       # 3 partitions, 161 rows: not folded
+    "at_once_161": (40, 4, 333, 8, 1, 128, 0),       # every item at once: folded
+    "over_256": (65, 4, 90, 8, 1, 64, 0),            # more rows than a folded append looks through
     "long": (2, 5, 16 * 300 + 2, 16, 1, 128, 4864),   # runs of more than 64 blocks, new rows of two blocks
 }
 
